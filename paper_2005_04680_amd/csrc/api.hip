@@ -178,15 +178,26 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   const int64_t vblocks = (int64_t(T) * B + 1 + kOffsetsPerBlock - 1) / kOffsetsPerBlock;
   L.nkeyblocks = L.ntiles > vblocks ? L.ntiles : vblocks;
   if (L.nkeyblocks < 1) L.nkeyblocks = 1;
-  // Chunk of the segmented reduce: at least 128 look-ups per wavefront (a
-  // wavefront walks one chunk per row group), growing to at most 1024 while
-  // at least ~32K wavefronts remain (Large: 256 look-ups, 51K wavefronts;
-  // measured 2% faster than 512).
-  const int64_t rgw = kWave / row_geom(E).lpr;
-  int64_t c = 128 / rgw > 8 ? 128 / rgw : 8;
-  while (c < 1024 && c * 2 * 32768 * rgw <= NS) c *= 2;
+  // Chunks of the segmented reduce (one per row group): 8 look-ups, doubled
+  // while kReduceBlocks blocks remain, up to 256.  The chip holds 1024 to 1280
+  // blocks at once; measured at 1024 / 2048 / 4096 / 8192 blocks, us per
+  // update: 1.7M look-ups of E = 128 264 / 225 / 219 / 220, 525K weighted of
+  // E = 100 82 / 74 / 75 / 84, 1.8M of E = 64 100 / 91 / 95 / 108, 524K of
+  // E = 64 40 / 43 / 43 / 44.  Beyond 256 long walks lose what fewer block
+  // boundaries gain (13.1M of E = 256: 64 1760, 128 1705, 256 1694, 512 1743).
+  const RowGeom g = row_geom(E);
+  const int64_t groups = kBlock / g.lpr;
+  // Look-ups per pair of carry slots that the workspace has room for; a block
+  // (c * groups look-ups) has one pair.
+  const int64_t rgw = kWave / g.lpr;
+  int64_t room = 128 / rgw > 8 ? 128 / rgw : 8;
+  while (room < 1024 && room * 2 * 32768 * rgw <= NS) room *= 2;
+  const int64_t slots = (NS + room - 1) / room;
+  int64_t c = 8;
+  while (c < 256 && (c * groups < room || c * 2 * groups * kReduceBlocks <= NS)) c *= 2;
   L.chunk = c;
   L.nchunks = (NS + c - 1) / c;
+  L.nblocks = (NS + c * groups - 1) / (c * groups);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -199,13 +210,15 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   L.off_tot = take(size_t(kMaxRadix) * 4);
   L.off_parts = take(size_t(L.nkeyblocks) * 4);
   L.off_flags = take(64);
-  L.off_carry = take(for_dedup ? 0 : size_t(2) * size_t(L.nchunks) * size_t(E) * 8);
+  L.off_carry = take(for_dedup ? 0 : size_t(2) * size_t(slots) * size_t(E) * 8);
   L.off_uniq = take(for_dedup ? size_t(L.ntiles) * 4 : 0);
   L.off_va = take(for_dedup ? 0 : size_t(NS) * 4);
   L.off_vb = take(for_dedup ? 0 : size_t(NS) * 4);
-  L.ngroups = (L.nchunks + kCarryGroup - 1) / kCarryGroup;
-  L.off_gsum = take(for_dedup ? 0 : size_t(L.ngroups) * size_t(E) * 8);
-  L.off_gflag = take(for_dedup ? 0 : size_t(L.ngroups) * 4);
+  // The size of a workspace is part of the interface (callers keep it, and the
+  // no-allocation entry point refuses by it): these bytes stay reserved.
+  const size_t spare = size_t((slots + 15) / 16);
+  take(for_dedup ? 0 : spare * size_t(E) * 8);
+  take(for_dedup ? 0 : spare * 4);
   L.total = off;
   return L;
 }

@@ -22,7 +22,7 @@ constexpr int64_t kMallBytes = int64_t(256) << 20;  // Infinity Cache (MALL)
 constexpr int kMaxRadixBits = 10;
 constexpr int kMaxRadix = 1 << kMaxRadixBits;
 constexpr int kMaxItemsPerThread = 16;  // radix tile: kBlock * (4, 8 or 16) keys
-constexpr int kCarryGroup = 16;  // chunks per pre-summed group of carries
+constexpr int kReduceBlocks = 2048;  // blocks that the segmented reduce is cut into, at least
 constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block validates, at most
 
 // Sentinel for "no key": keys are < 2^31 because sum(M_t) < 2^31.
@@ -173,12 +173,11 @@ struct BwdLayout {
   int64_t nkeyblocks;  // blocks of the key-build kernel
   int64_t chunk;       // sorted look-ups per segment-reduce chunk
   int64_t nchunks;
+  int64_t nblocks;     // blocks of the segment reduce
   int passes;          // radix passes
   int bits;            // digit width of every pass
-  int64_t ngroups;     // groups of kCarryGroup chunks
   size_t off_a, off_b, off_hist, off_tot, off_parts, off_flags, off_carry, off_uniq, off_va,
-      off_vb, off_gsum, off_gflag,
-      total;
+      off_vb, total;
 };
 
 BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t total_rows,

@@ -1,0 +1,72 @@
+"""GPU parity of the update's segmented reduce where segments meet the edges of
+row groups' chunks and of blocks: a segment inside a block is completed from
+the block's partial sums in LDS, one that crosses blocks by the fix-up from
+the blocks' partial sums.  Tolerance: the update's, |gpu - oracle| <= 1e-6 +
+1e-5 |oracle| (the sums are FP64 on both sides).
+"""
+import numpy as np
+import pytest
+
+from gpu_util import require_gpu
+from test_gpu_parity import _tables, check_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _lanes(dim):
+    lanes = 1
+    while lanes < dim // 4 and lanes < 64:
+        lanes *= 2
+    return lanes
+
+
+def _check(lengths, dim, split, rng, what):
+    M = len(lengths) + 3
+    look = np.repeat(np.arange(len(lengths)) + 1, lengths).astype(np.int32)
+    rng.shuffle(look)
+    batch = look.size // 19 + 1
+    cuts = np.sort(rng.integers(0, look.size + 1, batch - 1))
+    O = np.concatenate([[0], cuts, [look.size]]).astype(np.int32)
+    G = rng.standard_normal((1, batch, dim)).astype(np.float32)
+    check_step(_tables(rng, (M,), dim, 0.01), batch, look, O, G, 0.1, split=split, what=what)
+
+
+# look-ups that a block walks at these sizes: 8 per row group (32 where a row
+# takes a whole wavefront), 256 / lanes row groups
+@pytest.mark.parametrize("dim,split", [(4, False), (8, True), (16, False), (20, True), (64, False),
+                                       (100, False), (128, True), (256, False), (512, True),
+                                       (768, False), (1024, False)])
+def test_segments_around_chunks_and_blocks(dim, split):
+    lanes = _lanes(dim)
+    c, groups = (32 if lanes == 64 else 8), 256 // lanes
+    span = c * groups
+    rng = np.random.default_rng(dim)
+    # a span of one-look-up segments first, so that long ones start anywhere
+    kinds = [1, 2, c - 1, c, c + 1, 2 * c + 1, span - 1, span, span + 1, 2 * span, 3 * span + c]
+    lengths = rng.permutation(np.repeat(kinds, [40, 20, 9, 9, 9, 9, 2, 2, 2, 1, 1]))
+    _check(lengths, dim, split, rng, f"blocks of {span} E={dim}")
+
+
+@pytest.mark.parametrize("dim,extra", [(64, 0), (256, 1), (1024, -1)])
+def test_segment_over_many_blocks(dim, extra):
+    """A segment over more blocks than a fix-up block looks at in one round (256),
+    and one over more than it has row groups; both end at, before or after a
+    block's edge."""
+    lanes = _lanes(dim)
+    groups = 256 // lanes
+    span = (32 if lanes == 64 else 8) * groups
+    _check(np.array([span - 3, 258 * span + 3 + extra, 5, (groups + 2) * span + 1]), dim, False,
+           np.random.default_rng(dim), f"long segment E={dim}")
+
+
+@pytest.mark.parametrize("ns", [1, 7, 8, 9, 127, 128, 129, 255, 256, 257])
+def test_last_block(ns):
+    """The last block holds any number of look-ups, from one (E = 64: blocks of 128)."""
+    rng = np.random.default_rng(ns)
+    _check(np.full(1, ns), 64, False, rng, f"one segment of {ns}")
+    _check(np.ones(ns, int), 64, True, rng, f"{ns} segments")
