@@ -160,6 +160,17 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   L.passes = (nbits + kMaxRadixBits - 1) / kMaxRadixBits;
   L.bits = L.passes > 0 ? (nbits + L.passes - 1) / L.passes : 6;
   if (L.bits < 6) L.bits = 6;
+  // Tile by tile in LDS while that takes fewer and shorter kernels than the
+  // radix sort's nine (31 to 36 us whatever the size): up to 24 tiles and, the
+  // merge searching every tile of a table, 8 per table if the tables share the
+  // look-ups evenly.  Measured, us per prepare, radix / tiles: 512 look-ups 18.5
+  // / 6.6; 13K over 26 tables 34.0 / 12.1; 59K over 8 33.8 / 19.7; 81K over 3
+  // (7 tiles each) 31.0 / 23.7; 120K over 2 (15 each) 33.9 / 31.8; 102K in one
+  // table (25) 31.3 / 42.7.  With many more bags than look-ups the offsets are
+  // the work, and the radix sort's key build spreads them over more blocks.
+  L.small = NS > 0 && NS <= kSmallSort && NS <= int64_t(T) * kSmallPerTable &&
+            int64_t(T) * B <= (2 * NS > kSmallOffsets ? 2 * NS : kSmallOffsets);
+  L.sorted_in_b = !L.small && NS > 0 && L.passes % 2 == 1;
   // Radix tiles: the largest of 4096, 2048 or 1024 keys that still gives at
   // least 512 tiles (two per compute unit), but at least 2 keys per digit
   // value (a tile's scatter then writes runs, not single words; 1.7M keys of

@@ -25,6 +25,13 @@ constexpr int kMaxItemsPerThread = 16;  // radix tile: kBlock * (4, 8 or 16) key
 constexpr int kReduceBlocks = 2048;  // blocks that the segmented reduce is cut into, at least
 constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block validates, at most
 
+// Small calls: tiles of one table's look-ups that a block sorts in LDS, and
+// when a call is small (see backward_layout).
+constexpr int kSmallTile = 4096;
+constexpr int kSmallSort = 24 * kSmallTile;
+constexpr int kSmallPerTable = 8 * kSmallTile;
+constexpr int kSmallOffsets = 32768;
+
 // Sentinel for "no key": keys are < 2^31 because sum(M_t) < 2^31.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
@@ -176,6 +183,8 @@ struct BwdLayout {
   int64_t nblocks;     // blocks of the segment reduce
   int passes;          // radix passes
   int bits;            // digit width of every pass
+  bool small;          // sorted tile by tile (launch_sort_small)
+  bool sorted_in_b;    // which of the two buffers the sort ends in
   size_t off_a, off_b, off_hist, off_tot, off_parts, off_flags, off_carry, off_uniq, off_va,
       off_vb, total;
 };
@@ -191,14 +200,12 @@ uint32_t phase_token(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t total
 
 // The buffer that holds the sorted look-ups after the sort phase.
 inline uint64_t* sorted_buffer(const BwdLayout& L, char* ws) {
-  const int passes = L.ns > 0 ? L.passes : 0;
-  return reinterpret_cast<uint64_t*>(ws + (passes % 2 == 0 ? L.off_a : L.off_b));
+  return reinterpret_cast<uint64_t*>(ws + (L.sorted_in_b ? L.off_b : L.off_a));
 }
 
 // The per-look-up weights in sorted order (weighted bags), beside it.
 inline float* sorted_values(const BwdLayout& L, char* ws) {
-  const int passes = L.ns > 0 ? L.passes : 0;
-  return reinterpret_cast<float*>(ws + (passes % 2 == 0 ? L.off_va : L.off_vb));
+  return reinterpret_cast<float*>(ws + (L.sorted_in_b ? L.off_vb : L.off_va));
 }
 
 // Y is FP32 [T*B][E], or (y_bf16, split tables only) BF16 bit patterns.
@@ -212,6 +219,11 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
 hipError_t launch_sort(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
                        int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
                        uint32_t token, const float* A, hipStream_t st);
+
+// The same for a call with L.small.
+hipError_t launch_sort_small(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
+                             int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
+                             uint32_t token, const float* A, hipStream_t st);
 
 // dY is FP32 [T*B][E], or (dy_bf16, split tables only) BF16 bit patterns.
 hipError_t launch_segment_sgd(const TableDesc& d, bool split, int32_t B, const void* dY,
