@@ -4,6 +4,9 @@
 // their look-ups (contiguous in `indices`) as one list: U row loads are in
 // flight per lane before any of them is summed, and a bag's FP32 sum is
 // stored when the walk crosses the bag's end offset (empty bags store +0.0).
+// Where every bag of a wavefront holds one look-up its rows are copied without
+// that walk, which the issue of its instructions bounds: 1.7M bags of E = 128
+// (872 MB written) 249 -> 222-229 us, 53K 13.3 -> 9.0.
 // Every lane holds CPL groups of 4 columns, so a row is read with 128-bit
 // loads (64-bit for the BF16 halves of a split table).  Grids that fit the
 // chip at once give each XCD one contiguous range of bags (one or two tables,
@@ -67,7 +70,7 @@ __global__ __launch_bounds__(kBlock, MULTI ? (CPL == 1 && MODE == kPoolPlain ? 6
   const int lane = lane_id();
   const int rg = lane / LPR, rl = lane % LPR;
   const int blk = int(logical_block(in_order != 0));
-  const int item = (blk * kWavesPerBlock + wave_id()) * R + rg;
+  const int item = (blk * int(blockDim.x / kWave) + wave_id()) * R + rg;
   if (item >= items) return;
 
   const int TB = d.num_tables * B;
@@ -117,6 +120,48 @@ __global__ __launch_bounds__(kBlock, MULTI ? (CPL == 1 && MODE == kPoolPlain ? 6
     if (olanes && !bad && rl <= k1 - k0) ov = O[k0 + rl];
     bound = bad ? 0 : O[k0 + 1];
     bad = bad || bound < s0 || bound > s1;
+  }
+
+  // One look-up in every bag of the wavefront's row groups: the rows are
+  // copied (0.0 + x turns -0.0 into the sum's +0.0; a weight multiplies in
+  // FP64), without a walk along bag ends.
+  if constexpr (MULTI) {
+    const bool one = !olanes ? false : !bad && (rl > k1 - k0 || ov == s0 + rl);
+    if (__builtin_amdgcn_ballot_w64(!one) == 0ull) {
+      const int n = k1 - k0;
+      const int mine = rl < n ? I[s0 + rl] : 0;
+      float aw = 1.f;
+      if constexpr (MODE == kPoolWeighted) aw = rl < n ? A[s0 + rl] : 0.f;
+      for (int i = 0; i < G; i += U) {
+        f4 v[U][CPL];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int from = min(i + u, n - 1);
+          const int idx = __shfl(mine, rg * LPR + from, kWave);
+          ok[u] = uint32_t(idx) < M;
+          if (!ok[u]) err = EMBBAG_ERR_INDEX_RANGE;
+#pragma unroll
+          for (int j = 0; j < CPL; ++j)
+            v[u][j] = load_row4<SPLIT>(base, ok[u] ? uint32_t(idx) : 0u, E, min(rl + j * LPR, E4 - 1));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (i + u >= n) break;
+          d4 one_row[CPL];
+          double c = 1.0;
+          if constexpr (MODE == kPoolWeighted) c = double(__shfl(aw, rg * LPR + i + u, kWave));
+#pragma unroll
+          for (int j = 0; j < CPL; ++j) {
+            one_row[j] = d4{0.0, 0.0, 0.0, 0.0};
+            if (ok[u]) one_row[j] += MODE == kPoolWeighted ? c * to_d4(v[u][j]) : to_d4(v[u][j]);
+          }
+          store_bag(k0 + i + u, one_row, 1);
+        }
+      }
+      if (err != 0 && rl == 0 && status != nullptr) atomicMin(status, err);
+      return;
+    }
   }
 
   d4 acc[CPL];
@@ -252,22 +297,24 @@ __global__ void fwd_empty_check(const int32_t* __restrict__ O, int32_t NS,
 template <bool SPLIT, int MODE, bool YBF16, int LPR, int CPL>
 void launch_one(dim3 grid, hipStream_t st, const TableDesc& d, const int32_t* I, const int32_t* O,
                 int32_t NS, int32_t B, int32_t G, int32_t gpt, int32_t items, void* Y,
-                int32_t* status, const float* A, int32_t in_order) {
+                int32_t* status, const float* A, int32_t in_order, int threads) {
+#define EMB_ONE(MULTI)                                                                          \
+  hipLaunchKernelGGL((fwd_gather_sum<LPR, CPL, SPLIT, MULTI, MODE, YBF16>), grid,         \
+                     dim3(threads), 0, st, d, I, O, NS, B, G, gpt, items, Y, status, A, in_order)
   if (G > 1)
-    hipLaunchKernelGGL((fwd_gather_sum<LPR, CPL, SPLIT, true, MODE, YBF16>), grid, dim3(kBlock), 0,
-                       st, d, I, O, NS, B, G, gpt, items, Y, status, A, in_order);
+    EMB_ONE(true);
   else
-    hipLaunchKernelGGL((fwd_gather_sum<LPR, CPL, SPLIT, false, MODE, YBF16>), grid, dim3(kBlock),
-                       0, st, d, I, O, NS, B, G, gpt, items, Y, status, A, in_order);
+    EMB_ONE(false);
+#undef EMB_ONE
 }
 
 template <bool SPLIT, int MODE, bool YBF16 = false>
 bool dispatch(RowGeom g, dim3 grid, hipStream_t st, const TableDesc& d, const int32_t* I,
               const int32_t* O, int32_t NS, int32_t B, int32_t G, int32_t gpt, int32_t items,
-              void* Y, int32_t* status, const float* A, int32_t in_order) {
+              void* Y, int32_t* status, const float* A, int32_t in_order, int threads) {
 #define EMB_FWD(L, C)                                                                   \
   launch_one<SPLIT, MODE, YBF16, L, C>(grid, st, d, I, O, NS, B, G, gpt, items, Y, status, A, \
-                                       in_order)
+                                       in_order, threads)
   switch (g.lpr) {
     case 1: EMB_FWD(1, 1); return true;
     case 2: EMB_FWD(2, 1); return true;
@@ -297,17 +344,31 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
     hipLaunchKernelGGL(fwd_empty_check, dim3(1), dim3(kWave), 0, st, O, int32_t(NS), status);
     return hipGetLastError();
   }
-  // Bags per row group: enough look-ups per group to keep ~16 row loads per
-  // lane in flight when bags are short (P = 1 for the MLPerf-style tables).
-  const int64_t avg = NS / TB;
-  int G = avg >= 16 ? 1 : int(16 / (avg > 0 ? avg : 1));
-  G = G > 64 ? 64 : G;
-  G = G > B ? B : G;
-  const int gpt = (B + G - 1) / G;
-  const int64_t items = int64_t(d.num_tables) * gpt;
+  // Bags per row group.  A wavefront's loads go out once per group of bags
+  // (offsets, look-ups, rows), so short bags share a group: 16 bags of one
+  // look-up, 8 look-ups' worth of longer ones (of 3 look-ups, E = 64, 213K
+  // bags: 8 37 us, 16 42; of 8, E = 16, 66K bags: 7 and 14).  Groups shrink
+  // while the grid has fewer than kFillBlocks blocks (66K bags of 0 to 3,
+  // E = 64: 1024 blocks 11.6 us, 512 14.5), but bags of one look-up stay four
+  // to a group, where they are copied (13K bags of E = 128: four 4.6 us, two
+  // 5.2, one 6.7), and a group's offsets have to fit its lanes.
   const RowGeom g = row_geom(d.dim);
   const int per_block = kWavesPerBlock * (kWave / g.lpr);
-  const dim3 grid(unsigned((items + per_block - 1) / per_block));
+  constexpr int64_t kFillBlocks = 1024;
+  const int64_t avg = NS / TB;
+  int G = avg <= 1 ? 16 : (avg < 8 ? int(8 / avg) : 1);
+  if (g.lpr >= 4 && G >= g.lpr) G = g.lpr / 2;
+  G = G > B ? B : G;
+  const int least = avg <= 1 ? 4 : 1;
+  while (G > least && TB < kFillBlocks * per_block * G) G /= 2;
+  const int gpt = (B + G - 1) / G;
+  const int64_t items = int64_t(d.num_tables) * gpt;
+  // Blocks of one wavefront where four would leave compute units idle (128
+  // bags of E = 16: 2.9 us instead of 4.1).
+  const bool spread = items <= int64_t(kNumCu) * per_block;
+  const int threads = spread ? kWave : kBlock;
+  const int rows_per_block = threads / g.lpr;
+  const dim3 grid(unsigned((items + rows_per_block - 1) / rows_per_block));
   const int32_t ns = int32_t(NS), it = int32_t(items);
   // A table's touched rows are at most its look-ups' rows.
   const int64_t row_bytes = int64_t(d.dim) * (split ? 2 : 4);
@@ -315,19 +376,19 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
   bool ok = false;
   if (split && y_bf16)
     ok = dispatch<true, kPoolPlain, true>(g, grid, st, d, I, O, ns, B, G, gpt, it, Y, status,
-                                          nullptr, in_order);
+                                          nullptr, in_order, threads);
   else if (split)
     ok = dispatch<true, kPoolPlain>(g, grid, st, d, I, O, ns, B, G, gpt, it, Y, status, nullptr,
-                                    in_order);
+                                    in_order, threads);
   else if (pool.mode == kPoolWeighted)
     ok = dispatch<false, kPoolWeighted>(g, grid, st, d, I, O, ns, B, G, gpt, it, Y, status,
-                                        pool.weights, in_order);
+                                        pool.weights, in_order, threads);
   else if (pool.mode == kPoolMean)
     ok = dispatch<false, kPoolMean>(g, grid, st, d, I, O, ns, B, G, gpt, it, Y, status, nullptr,
-                                    in_order);
+                                    in_order, threads);
   else
     ok = dispatch<false, kPoolPlain>(g, grid, st, d, I, O, ns, B, G, gpt, it, Y, status, nullptr,
-                                     in_order);
+                                     in_order, threads);
   if (!ok) return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -1,0 +1,73 @@
+"""Forward of bags that hold one look-up each (copied) or nearly so: pooled
+outputs must be the oracle's bits, whatever the width, storage and pooling, at
+the edges of the groups of bags that a row group takes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2005_04680_amd as pk
+from gpu_util import DEV, GpuTables, bf16_bits, bits_equal, require_gpu, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def _bags(T, batch, kind, rng):
+    sizes = np.ones(T * batch, int)
+    if kind == "two and none":  # one look-up on average, not in every bag
+        sizes[3::11] = 2
+        sizes[5::11] = 0
+    elif kind == "first long":
+        sizes[0] = 40
+    O = np.r_[0, np.cumsum(sizes)].astype(np.int32)
+    return O
+
+
+@pytest.mark.parametrize("kind", ["one", "two and none", "first long"])
+@pytest.mark.parametrize("dim,batch", [(4, 5), (8, 300), (16, 17), (20, 4096), (64, 1), (64, 2047),
+                                       (128, 16), (128, 4001), (256, 33), (512, 5), (1024, 130)])
+def test_pooled_bits(dim, batch, kind):
+    rng = np.random.default_rng(dim + batch)
+    rows = (7, 4000, 1)
+    O = _bags(3, batch, kind, rng)
+    I = np.concatenate([rng.integers(0, m, O[(t + 1) * batch] - O[t * batch])
+                        for t, m in enumerate(rows)]).astype(np.int32)
+    W = [rng.standard_normal((m, dim)).astype(np.float32) for m in rows]
+    W[0][3] = -0.0
+    W[1][7::9] *= np.float32(1e-42)  # subnormal and tiny rows
+    print(dim, batch, kind, flush=True)
+    gt = GpuTables(W)
+    rc, Y = gt.forward(batch, I, O)
+    assert rc == 0 and gt.read_status() == 0
+    assert bits_equal(Y.cpu().numpy(), oracle.forward(W, batch, I, O)[1])
+    Id, Od = to_dev(I), to_dev(O)
+    a = rng.uniform(-2, 2, I.size).astype(np.float32)
+    for w, mode, om in ((a, pk.EMBBAG_POOL_SUM, oracle.POOL_SUM),
+                        (None, pk.EMBBAG_POOL_MEAN, oracle.POOL_MEAN)):
+        assert pk.embbag_forward_pooled(gt.w, batch, Id, Od, Y, None if w is None else to_dev(w),
+                                        mode, gt.status) == 0
+        assert bits_equal(Y.cpu().numpy(), oracle.forward_weighted(W, batch, I, O, w, om)[1])
+    gs = GpuTables(W, split=True)
+    his = [oracle.split(w)[0] for w in W]
+    rc, Y = gs.forward(batch, I, O)
+    assert rc == 0
+    assert bits_equal(Y.cpu().numpy(), oracle.forward_split(his, batch, I, O)[1])
+    Yb = torch.empty((3, batch, dim), dtype=torch.bfloat16, device=DEV)
+    assert pk.embbag_forward_split_bf16_act(gs.w, batch, Id, Od, Yb, gs.status) == 0
+    assert bits_equal(bf16_bits(Yb), oracle.forward_split_bf16_act(his, batch, I, O)[1])
+    assert gs.read_status() == 0
+
+
+@pytest.mark.parametrize("bad", [7, -1])
+def test_index_out_of_range(bad):
+    O = np.arange(3 * 700 + 1, dtype=np.int32)
+    I = np.zeros(2100, np.int32)
+    I[1399] = bad
+    gt = GpuTables([np.ones((7, 128), np.float32)] * 3)
+    rc, _ = gt.forward(700, I, O)
+    assert rc == 0 and gt.read_status() == pk.EMBBAG_ERR_INDEX_RANGE
