@@ -170,7 +170,18 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   // the work, and the radix sort's key build spreads them over more blocks.
   L.small = NS > 0 && NS <= kSmallSort && NS <= int64_t(T) * kSmallPerTable &&
             int64_t(T) * B <= (2 * NS > kSmallOffsets ? 2 * NS : kSmallOffsets);
-  L.sorted_in_b = !L.small && NS > 0 && L.passes % 2 == 1;
+  // Radix passes inside each table: two for tables of up to 2^20 rows instead
+  // of three, in four launches instead of nine.  A block of the scatter adds up
+  // the counts of its table's tiles by itself, so that the work grows with the
+  // square of the tiles per table.  Measured, us per prepare, whole list / by
+  // table: 120K look-ups over 2 tables 33.9 / 27.2; 300K over 40 42.2 / 31.2;
+  // 524K over 8 (16 tiles each) 43.9 / 32.6; 819K over 8 54.4 / 35.8; 525K
+  // weighted over 5 of 3M rows 52.2 / 42.6; 1.7M over 26 73.9 / 70.5; 400K in
+  // one table (98 tiles) 45.4 / 44.4; 1M in one (244) 44.6 / 60.7; 2M over 8
+  // 69.1 / 70.5; 13.1M over 16 253 / 372.
+  L.by_table = !L.small && NS > 0 && NS <= kTableSort && NS <= int64_t(T) * kTableSortPerTable &&
+               int64_t(T) * B <= 2 * NS;
+  L.sorted_in_b = !L.small && !L.by_table && NS > 0 && L.passes % 2 == 1;
   // Radix tiles: the largest of 4096, 2048 or 1024 keys that still gives at
   // least 512 tiles (two per compute unit), but at least 2 keys per digit
   // value (a tile's scatter then writes runs, not single words; 1.7M keys of

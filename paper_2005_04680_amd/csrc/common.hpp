@@ -25,12 +25,13 @@ constexpr int kMaxItemsPerThread = 16;  // radix tile: kBlock * (4, 8 or 16) key
 constexpr int kReduceBlocks = 2048;  // blocks that the segmented reduce is cut into, at least
 constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block validates, at most
 
-// Small calls: tiles of one table's look-ups that a block sorts in LDS, and
-// when a call is small (see backward_layout).
-constexpr int kSmallTile = 4096;
-constexpr int kSmallSort = 24 * kSmallTile;
-constexpr int kSmallPerTable = 8 * kSmallTile;
+// Which calls are sorted table by table, in tiles of 4096 look-ups (see
+// backward_layout).
+constexpr int kSmallSort = 24 * 4096;
+constexpr int kSmallPerTable = 8 * 4096;
 constexpr int kSmallOffsets = 32768;
+constexpr int64_t kTableSort = 448 * 4096;
+constexpr int64_t kTableSortPerTable = 64 * 4096;
 
 // Sentinel for "no key": keys are < 2^31 because sum(M_t) < 2^31.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
@@ -183,7 +184,8 @@ struct BwdLayout {
   int64_t nblocks;     // blocks of the segment reduce
   int passes;          // radix passes
   int bits;            // digit width of every pass
-  bool small;          // sorted tile by tile (launch_sort_small)
+  bool small;          // tiles sorted and merged (launch_sort_small)
+  bool by_table;       // radix passes inside each table (launch_sort_tables)
   bool sorted_in_b;    // which of the two buffers the sort ends in
   size_t off_a, off_b, off_hist, off_tot, off_parts, off_flags, off_carry, off_uniq, off_va,
       off_vb, total;
@@ -224,6 +226,11 @@ hipError_t launch_sort(const TableDesc& d, int32_t B, const int32_t* I, const in
 hipError_t launch_sort_small(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
                              int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
                              uint32_t token, const float* A, hipStream_t st);
+
+// The same for a call with L.by_table.
+hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
+                              int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
+                              uint32_t token, const float* A, hipStream_t st);
 
 // dY is FP32 [T*B][E], or (dy_bf16, split tables only) BF16 bit patterns.
 hipError_t launch_segment_sgd(const TableDesc& d, bool split, int32_t B, const void* dY,

@@ -13,7 +13,7 @@
 // ballots give each lane its rank among equal digits) and written out in
 // digit order, so that the global stores form runs of consecutive addresses.
 // No kernel waits on another workgroup.  Small calls are sorted tile by tile
-// instead (sort_small.hip).
+// instead (sort_small.hip), mid-sized ones table by table (sort_tables.hip).
 //
 // Look-up positions are unsigned 32-bit: num_indices may be 2^31 - 1, and a
 // tile's last slots run past it (by less than a tile), which stays below 2^32.
@@ -657,6 +657,7 @@ void unique_launch(const uint64_t* sorted, const BwdLayout& L, uint32_t* counts,
 hipError_t launch_sort(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
                        int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
                        uint32_t token, const float* A, hipStream_t st) {
+  if (L.by_table) return launch_sort_tables(d, B, I, O, NS, L, ws, d_status, token, A, st);
   if (L.small) return launch_sort_small(d, B, I, O, NS, L, ws, d_status, token, A, st);
   switch (L.bits) {
     case 6: return sort_ipt<6>(d, B, I, O, NS, L, ws, d_status, token, A, st);

@@ -1,0 +1,262 @@
+// Keys and stable radix sort of a mid-sized call's look-ups, table by table.
+//
+// The look-ups of a table are one contiguous range already, so a radix pass
+// inside each table needs no digit of the table: digits of up to 10 bits cover
+// tables of 2^20 rows in two passes.  A tile (4096 look-ups of one table) is a
+// block of 16 wavefronts with a digit per thread.  No kernel scans the tiles'
+// counts: a table has few tiles, and each block of the scatter adds up those
+// of its own (16 of them are 32 KB of 16-bit counts, read from the L2 in one
+// round) while it ranks its keys.
+//
+// Bound by latency: at 524K look-ups over 8 tables (132 blocks) the keys take
+// 7 us, a scatter 10 (the counts' sums, the ranks, four barriers, the store of
+// runs of 4 keys), the second pass's counts 4; three passes of 8 bits over the
+// whole list took 6 + 3 * (4 + 7) + 2 * 3 in nine launches.
+//
+// The result is that of the whole list's radix sort, bit for bit.
+#include "sort_tile.hpp"
+
+namespace embbag {
+namespace {
+
+// Keys of one tile and its counts of the first digit; `vb` of the offsets.
+__global__ __launch_bounds__(kThreads) void table_keys(
+    TableDesc d, const int32_t* __restrict__ I, const int32_t* __restrict__ O, int32_t NS,
+    int32_t B, int32_t TB, int32_t vb, int32_t bits, uint64_t* __restrict__ out,
+    uint16_t* __restrict__ hist, Tile* __restrict__ info, int32_t* __restrict__ status) {
+  __shared__ uint32_t lbag[kTile];
+  __shared__ uint32_t lhist[1 << kMaxDigitBits];
+  __shared__ int32_t krange[2];
+  __shared__ int32_t lerr;
+  const int tid = threadIdx.x, blk = int(blockIdx.x);
+  int err = 0;
+  if (tid == 0) lerr = 0;
+  lhist[tid] = 0;
+  const Tile me = find_tile(O, NS, d.num_tables, B, blk);
+  if (tid == 0) info[blk] = me;
+  const int start = me.start, count = me.count, t = me.table;
+  int32_t rv[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int j = i * kThreads + tid;
+    rv[i] = j < count ? I[start + j] : 0;
+  }
+  const int64_t k0 = int64_t(blk) * vb;
+  if (bad_offsets(O, k0, min(k0 + vb, int64_t(TB)), NS, TB)) err = EMBBAG_ERR_OFFSETS;
+  if (count > 0) {
+    if (fill_bags<false>(O, t * B, t * B + B - 1, start, count, NS, TB, lbag, krange))
+      err = EMBBAG_ERR_OFFSETS;
+    const uint32_t rows = d.rows[t], base = d.rowbase[t], mask = (1u << bits) - 1u;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int j = i * kThreads + tid;
+      if (j < count) {
+        uint32_t r = uint32_t(rv[i]);
+        if (r >= rows) {
+          err = min(err, EMBBAG_ERR_INDEX_RANGE);
+          r = 0;
+        }
+        out[start + j] = (uint64_t(base + r) << 32) | min(lbag[j], uint32_t(TB - 1));
+        atomicAdd(&lhist[r & mask], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  if (count > 0 && tid <= int((1u << bits) - 1u))
+    hist[(size_t(blk) << bits) + tid] = uint16_t(lhist[tid]);
+  if (err != 0) atomicMin(&lerr, err);
+  __syncthreads();
+  if (tid == 0) status[blk] = lerr;
+}
+
+// A tile's counts of the digit at `shift`.  The keys arrive in the previous
+// pass's order, so equal digits often come in runs: the first lane of each run
+// in a wavefront adds the run's length.
+__global__ __launch_bounds__(kThreads) void table_counts(
+    TableDesc d, const uint64_t* __restrict__ src, const Tile* __restrict__ info, int32_t shift,
+    int32_t bits, uint16_t* __restrict__ hist) {
+  __shared__ uint32_t lhist[1 << kMaxDigitBits];
+  const int tid = threadIdx.x, lane = lane_id(), blk = int(blockIdx.x);
+  const Tile me = info[blk];
+  if (me.count <= 0) return;
+  lhist[tid] = 0;
+  uint32_t kv[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int j = i * kThreads + tid;
+    kv[i] = j < me.count ? key_of(src[me.start + j]) : 0u;
+  }
+  __syncthreads();
+  const uint32_t base = d.rowbase[me.table], R = 1u << bits;
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const uint32_t dg =
+        i * kThreads + tid < me.count ? ((kv[i] - base) >> shift) & (R - 1u) : R;
+    const uint32_t left = __shfl_up(dg, 1, kWave);
+    const bool head = lane == 0 || dg != left;
+    const uint64_t heads = __builtin_amdgcn_ballot_w64(head);
+    if (head && dg < R) {
+      const uint64_t after = lane == kWave - 1 ? 0ull : heads >> (lane + 1);
+      atomicAdd(&lhist[dg], after ? uint32_t(__builtin_ctzll(after)) + 1u : uint32_t(kWave - lane));
+    }
+  }
+  __syncthreads();
+  if (tid < int(R)) hist[(size_t(blk) << bits) + tid] = uint16_t(lhist[tid]);
+}
+
+// Stable scatter of a tile by the digit at `shift` inside its table.  A block
+// sums the counts of its table's tiles by itself: R 16-bit counts a tile, two
+// to a word, the block's threads taking as many tiles at a time as they span.
+// FIRST: one more block folds the status words.
+template <bool VALS, bool FIRST>
+__global__ __launch_bounds__(kThreads) void table_scatter(
+    TableDesc d, const uint64_t* __restrict__ src, uint64_t* __restrict__ dst,
+    const Tile* __restrict__ info, int32_t shift, int32_t bits,
+    const uint16_t* __restrict__ hist, const float* __restrict__ vsrc, float* __restrict__ vdst,
+    const int32_t* __restrict__ status, int32_t nblocks, int32_t* __restrict__ flags,
+    int32_t* __restrict__ d_status, uint32_t token) {
+  __shared__ uint64_t buf[kTile];
+  __shared__ float vbuf[VALS ? kTile : 1];
+  __shared__ __align__(4) uint16_t whist[kWaves << kMaxDigitBits];
+  __shared__ uint32_t tot[1 << kMaxDigitBits], pre[1 << kMaxDigitBits];
+  __shared__ uint32_t scratch[2][kWaves];
+  const int tid = threadIdx.x, lane = lane_id(), w = wave_id(), blk = int(blockIdx.x);
+  if (FIRST && blk == nblocks) {
+    __shared__ int32_t lerr;
+    if (tid == 0) lerr = 0;
+    __syncthreads();
+    int e = 0;
+    for (int i = tid; i < nblocks; i += kThreads) e = min(e, status[i]);
+    if (e != 0) atomicMin(&lerr, e);
+    __syncthreads();
+    if (tid == 0) publish(lerr, token, flags, d_status);
+    return;
+  }
+  const Tile me = info[blk];
+  if (me.count <= 0) return;
+  const int count = me.count, R = 1 << bits;
+  const int ipt = (count + kThreads - 1) / kThreads;
+  const int j0 = w * (kWave * ipt) + lane;
+  uint64_t item[kItems];
+  float val[VALS ? kItems : 1];
+  bool valid[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int j = j0 + i * kWave;
+    valid[i] = i < ipt && j < count;
+    item[i] = valid[i] ? src[me.start + j] : 0ull;
+    if constexpr (VALS) val[i] = valid[i] ? vsrc[me.start + j] : 0.f;
+  }
+  // Counts of the table's tiles: all (tot) and before this one (pre).
+  tot[tid] = 0;
+  pre[tid] = 0;
+  for (int i = tid; i < (kWaves << bits) / 2; i += kThreads)
+    reinterpret_cast<uint32_t*>(whist)[i] = 0;
+  __syncthreads();
+  {
+    const int words = R / 2, col = tid & (words - 1), lead = tid / words;
+    const int stride = kThreads / words;  // words <= 512
+    const uint32_t* h = reinterpret_cast<const uint32_t*>(hist) + size_t(me.first) * words + col;
+    const int mine = blk - me.first;
+    uint32_t t0 = 0, t1 = 0, p0 = 0, p1 = 0;
+    constexpr int Q = 8;
+    for (int r0 = lead; r0 < me.tiles; r0 += stride * Q) {
+      uint32_t c[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        c[q] = r0 + q * stride < me.tiles ? h[size_t(r0 + q * stride) * words] : 0u;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const bool before = r0 + q * stride < mine;
+        t0 += c[q] & 0xFFFFu;
+        t1 += c[q] >> 16;
+        p0 += before ? c[q] & 0xFFFFu : 0u;
+        p1 += before ? c[q] >> 16 : 0u;
+      }
+    }
+    if (t0) atomicAdd(&tot[2 * col], t0);
+    if (t1) atomicAdd(&tot[2 * col + 1], t1);
+    if (p0) atomicAdd(&pre[2 * col], p0);
+    if (p1) atomicAdd(&pre[2 * col + 1], p1);
+  }
+  const uint32_t base = d.rowbase[me.table];
+  uint32_t dig[kItems], rank[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) dig[i] = ((key_of(item[i]) - base) >> shift) & uint32_t(R - 1);
+  rank_digits(dig, valid, ipt, bits, whist, rank);
+  __syncthreads();
+  const uint32_t mine_tot = tid < R ? tot[tid] : 0u;
+  const uint32_t to = scan_block(mine_tot, scratch[0]) + (tid < R ? pre[tid] : 0u);
+  const uint32_t first = place_digits(bits, whist, scratch[1]);
+  __syncthreads();
+  // (tot is free: it now holds a digit's place in the table less that in the tile)
+  if (tid < R) tot[tid] = to - first;
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    if (valid[i]) {
+      const uint32_t at = whist[(w << bits) + dig[i]] + rank[i];
+      buf[at] = item[i];
+      if constexpr (VALS) vbuf[at] = val[i];
+    }
+  }
+  __syncthreads();
+  const int begin = me.start - (blk - me.first) * kTile;
+  for (int j = tid; j < count; j += kThreads) {
+    const uint64_t it = buf[j];
+    const uint32_t g = ((key_of(it) - base) >> shift) & uint32_t(R - 1);
+    const uint32_t at = uint32_t(begin) + tot[g] + uint32_t(j);
+    dst[at] = it;
+    if constexpr (VALS) vdst[at] = vbuf[j];
+  }
+}
+
+}  // namespace
+
+hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
+                              int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
+                              uint32_t token, const float* A, hipStream_t st) {
+  const int32_t TB = d.num_tables * B, ns = int32_t(NS);
+  uint32_t rows = 2;  // of the largest table: its bits decide the digits
+  for (int t = 0; t < d.num_tables; ++t) rows = d.rows[t] > rows ? d.rows[t] : rows;
+  const int nbits = 32 - __builtin_clz(rows - 1u);
+  const int passes = (nbits + kMaxDigitBits - 1) / kMaxDigitBits;
+  const int bits = (nbits + passes - 1) / passes;
+  const int blocks = tile_blocks(NS, d.num_tables);
+  const int32_t vb = (TB + blocks - 1) / blocks;
+  uint16_t* hist = reinterpret_cast<uint16_t*>(ws + L.off_hist);
+  Tile* info = reinterpret_cast<Tile*>(hist + (size_t(blocks) << bits));
+  int32_t* status = reinterpret_cast<int32_t*>(info + blocks);
+  int32_t* flags = reinterpret_cast<int32_t*>(ws + L.off_flags);
+  // the last pass ends in the first buffer
+  uint64_t* src = reinterpret_cast<uint64_t*>(ws + (passes % 2 ? L.off_b : L.off_a));
+  uint64_t* dst = reinterpret_cast<uint64_t*>(ws + (passes % 2 ? L.off_a : L.off_b));
+  float* vdst = reinterpret_cast<float*>(ws + (passes % 2 ? L.off_va : L.off_vb));
+  float* vother = reinterpret_cast<float*>(ws + (passes % 2 ? L.off_vb : L.off_va));
+  const float* vsrc = A;  // the first pass reads the caller's weights
+  hipLaunchKernelGGL(table_keys, dim3(blocks), dim3(kThreads), 0, st, d, I, O, ns, B, TB, vb, bits,
+                     src, hist, info, status);
+  for (int p = 0; p < passes; ++p) {
+    const int shift = p * bits;
+    if (p > 0)
+      hipLaunchKernelGGL(table_counts, dim3(blocks), dim3(kThreads), 0, st, d, src, info, shift,
+                         bits, hist);
+#define EMB_SCATTER(VALS, FIRST)                                                                 \
+  hipLaunchKernelGGL((table_scatter<VALS, FIRST>), dim3(blocks + (FIRST ? 1 : 0)),               \
+                     dim3(kThreads), 0, st, d, src, dst, info, shift, bits, hist, vsrc, vdst,    \
+                     status, blocks, flags, d_status, token)
+    if (A != nullptr && p == 0) EMB_SCATTER(true, true);
+    else if (A != nullptr) EMB_SCATTER(true, false);
+    else if (p == 0) EMB_SCATTER(false, true);
+    else EMB_SCATTER(false, false);
+#undef EMB_SCATTER
+    uint64_t* t = src;
+    src = dst;
+    dst = t;
+    vsrc = vdst;
+    vdst = vother;
+    vother = const_cast<float*>(vsrc);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace embbag

@@ -1,4 +1,4 @@
-"""Small calls sort tile by tile in LDS: the sorted (key, bag) words, unique
+"""Small calls sort tile by tile in LDS, mid-sized ones table by table: the sorted (key, bag) words, unique
 keys and segment offsets must be those of a stable sort, bit for bit, at the
 edges of tiles (4096 look-ups of a table), of the one-block form (4096 in all)
 and of the path's range; data errors are reported as by the radix sort.
@@ -55,6 +55,15 @@ CASES = {
     "more bags than a block's threads": ((70000, 800), 9000, (12289, 5000)),
     "last size of the path": ((200000,) * 4, 3000, (30000, 30000, 30000, 8304)),
     "first size past it": ((200000,) * 4, 3000, (30000, 30000, 30000, 8305)),
+    "by table, one row each": ((1, 1), 700, (60000, 40000)),
+    "by table, one pass": ((1000, 3, 1024), 9000, (40960, 4097, 90000)),
+    "by table, two passes": ((1 << 20, 700, 5), 50, (0, 100000, 4096)),
+    "by table, three passes": ((1 << 20, (1 << 20) + 1), 50000, (99999, 8193)),
+    "by table, four passes": ((2147483000,), 3000, (32769,)),
+    "by table, 64 tables": ((50000,) * 64, 40, (1,) * 31 + (0,) + (3300,) * 32),
+    "by table, last per table": ((300000,), 900, (262144,)),
+    "whole list, first per table": ((300000,), 900, (262145,)),
+    "by table, most skewed": ((300000, 5, 5, 5, 5, 5, 5), 900, (1835008, 0, 0, 0, 0, 0, 0)),
 }
 
 
@@ -74,7 +83,7 @@ def test_sorted_as_by_a_stable_sort(name, hot):
     assert np.array_equal(got["seg_off"], seg)
 
 
-@pytest.mark.parametrize("counts", [(3000, 1000), (9000, 4000)])
+@pytest.mark.parametrize("counts", [(3000, 1000), (9000, 4000), (70000, 60000)])
 def test_data_errors(counts):
     rows, batch = (500, 800), 300
     rng = np.random.default_rng(3)
@@ -99,7 +108,7 @@ def test_data_errors(counts):
     assert rc == 0 and status == 0
 
 
-@pytest.mark.parametrize("counts", [(2000, 1500), (9000, 4097)])
+@pytest.mark.parametrize("counts", [(2000, 1500), (9000, 4097), (50000, 70000)])
 def test_weights_travel_with_the_look_ups(counts):
     rows, batch, dim = (900, 40000), 77, 12
     rng = np.random.default_rng(5)
