@@ -42,46 +42,79 @@
 namespace embbag {
 namespace {
 
-// Row update for FP32 tables: w <- fl(w - lr * G), G in FP64.
+template <class T>
+using Global = __attribute__((address_space(1))) T*;
+
+// Element `off` of a row of S at `row`, as a pointer to V.
+template <class V, class S>
+__device__ __forceinline__ Global<V> at(Global<S> row, int off) {
+  return (Global<V>)(row + off);
+}
+
+// Row update for FP32 tables: w <- fl(w - lr * G), G in FP64.  A Row is where a
+// row of a table lies (kept from its load to its store), a Pre what it holds.
 struct Fp32Rows {
+  struct Table {
+    Global<float> w;
+  };
+  struct Row {
+    Global<float> w;
+  };
   struct Pre {
     f4 w;
   };
   template <class D>
-  static __device__ __forceinline__ Pre load(const D& d, int t, uint32_t r, uint32_t E, int c4) {
-    return {__builtin_nontemporal_load(table_elem<const f4, float>(d.w[t], size_t(r) * E + c4 * 4))};
+  static __device__ __forceinline__ Table table(const D& d, int t) {
+    return {(Global<float>)static_cast<float*>(d.w[t])};
   }
-  template <class D>
-  static __device__ __forceinline__ void store(const D& d, int t, uint32_t r, uint32_t E, int c4,
-                                               const Pre& p, const d4& g, double lr) {
+  static __device__ __forceinline__ Row row(const Table& t, uint32_t r, uint32_t E) {
+    return {t.w + size_t(r) * E};
+  }
+  static __device__ __forceinline__ Pre load(const Row& r, int c4) {
+    return {__builtin_nontemporal_load(at<const f4>(r.w, c4 * 4))};
+  }
+  static __device__ __forceinline__ void store(const Row& r, int c4, const Pre& p, const d4& g,
+                                               double lr) {
     f4 o;
     o.x = float(double(p.w.x) - lr * g.x);
     o.y = float(double(p.w.y) - lr * g.y);
     o.z = float(double(p.w.z) - lr * g.z);
     o.w = float(double(p.w.w) - lr * g.w);
-    __builtin_nontemporal_store(o, table_elem<f4, float>(d.w[t], size_t(r) * E + c4 * 4));
+    __builtin_nontemporal_store(o, at<f4>(r.w, c4 * 4));
   }
 };
 
 // Row update for split tables (Section VII): recombine hi/lo into the FP32
 // weight, apply the FP32 update, split the result again.
 struct SplitRows {
+  struct Table {
+    Global<uint16_t> hi, lo;
+  };
+  struct Row {
+    Global<uint16_t> hi, lo;
+  };
   struct Pre {
     u2 hi, lo;
   };
   template <class D>
-  static __device__ __forceinline__ Pre load(const D& d, int t, uint32_t r, uint32_t E, int c4) {
-    const size_t off = size_t(r) * E + c4 * 4;
-    return {__builtin_nontemporal_load(table_elem<const u2, uint16_t>(d.w[t], off)),
-            __builtin_nontemporal_load(table_elem<const u2, uint16_t>(d.lo[t], off))};
+  static __device__ __forceinline__ Table table(const D& d, int t) {
+    return {(Global<uint16_t>)static_cast<uint16_t*>(d.w[t]),
+            (Global<uint16_t>)static_cast<uint16_t*>(d.lo[t])};
+  }
+  static __device__ __forceinline__ Row row(const Table& t, uint32_t r, uint32_t E) {
+    const size_t off = size_t(r) * E;
+    return {t.hi + off, t.lo + off};
+  }
+  static __device__ __forceinline__ Pre load(const Row& r, int c4) {
+    return {__builtin_nontemporal_load(at<const u2>(r.hi, c4 * 4)),
+            __builtin_nontemporal_load(at<const u2>(r.lo, c4 * 4))};
   }
   static __device__ __forceinline__ float upd(uint32_t hi16, uint32_t lo16, double g, double lr) {
     const float w = __uint_as_float((hi16 << 16) | lo16);
     return float(double(w) - lr * g);
   }
-  template <class D>
-  static __device__ __forceinline__ void store(const D& d, int t, uint32_t r, uint32_t E, int c4,
-                                               const Pre& p, const d4& g, double lr) {
+  static __device__ __forceinline__ void store(const Row& r, int c4, const Pre& p, const d4& g,
+                                               double lr) {
     const uint32_t w0 = __float_as_uint(upd(p.hi.x & 0xFFFFu, p.lo.x & 0xFFFFu, g.x, lr));
     const uint32_t w1 = __float_as_uint(upd(p.hi.x >> 16, p.lo.x >> 16, g.y, lr));
     const uint32_t w2 = __float_as_uint(upd(p.hi.y & 0xFFFFu, p.lo.y & 0xFFFFu, g.z, lr));
@@ -91,9 +124,8 @@ struct SplitRows {
     hi.y = (w2 >> 16) | (w3 & 0xFFFF0000u);
     lo.x = (w0 & 0xFFFFu) | (w1 << 16);
     lo.y = (w2 & 0xFFFFu) | (w3 << 16);
-    const size_t off = size_t(r) * E + c4 * 4;
-    __builtin_nontemporal_store(hi, table_elem<u2, uint16_t>(d.w[t], off));
-    __builtin_nontemporal_store(lo, table_elem<u2, uint16_t>(d.lo[t], off));
+    __builtin_nontemporal_store(hi, at<u2>(r.hi, c4 * 4));
+    __builtin_nontemporal_store(lo, at<u2>(r.lo, c4 * 4));
   }
 };
 
@@ -204,29 +236,46 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
     for (int u = 0; u < U; ++u) an[u] = lo + u < hi ? pd.svals[lo + u] : 0.f;
   }
   const uint64_t p0 = pn[0];
-  const bool first_open = lo < hi && kprev == key_of(p0);  // first segment began before lo
-  bool is_first = true;
+  // The first segment began before lo (and still is the one being summed).
+  const bool before = lo < hi && kprev == key_of(p0);
+  bool open = before;
   uint32_t cur = key_of(p0);
-  int ct = table_of_bag(bag_of(p0), B, inv_b);
+  // The table at hand: keys [kfirst, kend).  Keys increase, so it is looked up
+  // again only where a walk crosses into the next one, and a row's place is
+  // kept from its load to its store: at narrow rows the issue of instructions
+  // takes a third of the time (75 -> about 50 per look-up of four row groups;
+  // 525K weighted look-ups of E = 100 74 -> 70 us, 81K of E = 512 54 -> 51, 13.1M
+  // split of E = 256 1750 -> 1700).
+  uint32_t kfirst = 0, kend = 0;
+  typename Rows::Table tab;
+  auto row_of = [&](uint64_t word) {
+    if (key_of(word) >= kend) {
+      const int t = table_of_bag(bag_of(word), B, inv_b);
+      kfirst = tb.rowbase[t];
+      kend = tb.rowbase[t + 1];
+      tab = Rows::table(tb, t);
+    }
+    return Rows::row(tab, key_of(word) - kfirst, E);
+  };
 
   d4 acc[CPL];
   f4 glast[CPL];
+  int col[CPL];  // columns past the row's end load its last ones and store nothing
+  typename Rows::Row row;
   typename Rows::Pre pre[CPL];
+  if (lo < hi) row = row_of(p0);
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
     acc[j] = d4{0.0, 0.0, 0.0, 0.0};
     glast[j] = f4{0.f, 0.f, 0.f, 0.f};
-    const int c4 = rl + j * LPR;
-    if (lo < hi && !first_open && c4 < E4)
-      pre[j] = Rows::load(tb, ct, cur - tb.rowbase[ct], E, c4);
+    col[j] = min(rl + j * LPR, E4 - 1);
+    if (lo < hi && !open) pre[j] = Rows::load(row, col[j]);
   }
 
-  auto apply = [&](uint32_t key, int t) {
-    const uint32_t r = key - tb.rowbase[t];
+  auto apply = [&]() {
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
-      const int c4 = rl + j * LPR;
-      if (c4 < E4) Rows::store(tb, t, r, E, c4, pre[j], acc[j], lrd);
+      if (rl + j * LPR < E4) Rows::store(row, col[j], pre[j], acc[j], lrd);
     }
   };
   auto park = [&]() {
@@ -234,6 +283,11 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
     for (int j = 0; j < CPL; ++j) part[(grp * CPL + j) * LPR + rl] = acc[j];
   };
 
+  // Look-ups past hi: only in the grid's last blocks.
+  const bool ragged = uint64_t(uint32_t(blk) + 1u) * NG * uint32_t(C) > uint32_t(NS);
+  // A repeat of the previous look-up's (key, bag) reuses its dY row, where the
+  // wavefront is one row group; among several it costs more than the L1 hit.
+  constexpr bool kDup = LPR == kWave;
   uint64_t plast = p0;  // look-up before the current group (none before lo: p0 itself)
   for (uint32_t s = lo; s < hi; s += U) {
     uint64_t p[U];
@@ -242,44 +296,41 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
     int32_t ob0[U], ob1[U];
     bool dup[U], nseg[U];
     typename Dy<GBF16>::Raw g[U][CPL];
+    typename Rows::Row wr[U];
     typename Rows::Pre wp[U][CPL];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       p[u] = pn[u];
       if constexpr (kW) aw[u] = an[u];
-      bg[u] = s + u < hi ? bag_of(p[u]) : 0u;
+      bg[u] = bag_of(p[u]);  // bag 0 past hi
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint64_t pq = u == 0 ? plast : p[u - 1];
-      const bool valid = s + u < hi;
-      // a repeat of the previous look-up's (key, bag): its dY row is reused
-      dup[u] = valid && p[u] == pq && !(s == lo && u == 0);
+      const bool valid = !ragged || s + u < hi;
+      dup[u] = kDup && p[u] == pq && !(s == lo && u == 0);
       nseg[u] = valid && key_of(p[u]) != key_of(pq);
     }
     if constexpr (MODE == kPoolMean) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        ob0[u] = s + u < hi ? pd.offsets[bg[u]] : 0;
-        ob1[u] = s + u < hi ? pd.offsets[bg[u] + 1] : 1;
+        ob0[u] = pd.offsets[bg[u]];
+        ob1[u] = pd.offsets[bg[u] + 1];
       }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool ld = s + u < hi && !dup[u];
 #pragma unroll
       for (int j = 0; j < CPL; ++j) {
-        const int c4 = rl + j * LPR;
-        g[u][j] = (ld && c4 < E4) ? Dy<GBF16>::load(dY, bg[u], E, c4) : Dy<GBF16>::zero();
+        if (kDup && dup[u])
+          g[u][j] = Dy<GBF16>::zero();
+        else
+          g[u][j] = Dy<GBF16>::load(dY, bg[u], E, col[j]);
       }
       if (nseg[u]) {
-        const int tu = table_of_bag(bg[u], B, inv_b);
-        const uint32_t ru = key_of(p[u]) - tb.rowbase[tu];
+        wr[u] = row_of(p[u]);
 #pragma unroll
-        for (int j = 0; j < CPL; ++j) {
-          const int c4 = rl + j * LPR;
-          if (c4 < E4) wp[u][j] = Rows::load(tb, tu, ru, E, c4);
-        }
+        for (int j = 0; j < CPL; ++j) wp[u][j] = Rows::load(wr[u], col[j]);
       }
     }
 #pragma unroll
@@ -290,15 +341,15 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (s + u >= hi) break;
+      if (ragged && s + u >= hi) break;
       if (nseg[u]) {
-        if (is_first && first_open)
+        if (open)
           park();
         else
-          apply(cur, ct);
+          apply();
+        open = false;
         cur = key_of(p[u]);
-        ct = table_of_bag(bg[u], B, inv_b);
-        is_first = false;
+        row = wr[u];
 #pragma unroll
         for (int j = 0; j < CPL; ++j) {
           acc[j] = d4{0.0, 0.0, 0.0, 0.0};
@@ -310,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
       if constexpr (MODE == kPoolMean) c = 1.0 / double(ob1[u] - ob0[u]);
 #pragma unroll
       for (int j = 0; j < CPL; ++j) {
-        if (!dup[u]) glast[j] = Dy<GBF16>::value(g[u][j]);
+        if (!kDup || !dup[u]) glast[j] = Dy<GBF16>::value(g[u][j]);
         if constexpr (MODE == kPoolPlain)
           acc[j] += widen(glast[j]);
         else
@@ -324,12 +375,12 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
   // and parked; ending here, it is applied; begun here and going on, it waits
   // for the partial sums of the row groups that follow.
   const bool last_open = lo < hi && knext == cur;
-  const bool whole = is_first && first_open;
+  const bool whole = open;
   if (rl == 0) thru[grp] = whole && last_open;
   if (whole)
     park();
   else if (lo < hi && !last_open)
-    apply(cur, ct);
+    apply();
   __syncthreads();
   if (lo < hi && !whole && last_open) {
     int k = grp + 1;
@@ -341,11 +392,11 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
       ++k;
     }
     if (!on)
-      apply(cur, ct);
+      apply();
     else
       store_carry<CPL>(carry, 2 * int64_t(blk) + 1, E, rl, LPR, acc);
   }
-  if (grp == 0 && first_open) {
+  if (grp == 0 && before) {
     int k = 0;
     bool on = true;
 #pragma unroll
@@ -398,14 +449,14 @@ __global__ __launch_bounds__(kBlock) void segment_fixup(
   d4 first[CPL], acc[CPL];
   if (b + 1 + grp < nblocks) slot(2 * int64_t(b + 1 + grp), first);
   const int ct = table_of_bag(bag_of(wl), B, inv_b);
-  const uint32_t r = kl - d.rowbase[ct];
+  const typename Rows::Row row = Rows::row(Rows::table(d, ct), kl - d.rowbase[ct], E);
   typename Rows::Pre pre[CPL];
   if (grp == 0) {
     slot(2 * int64_t(b) + 1, acc);
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
       const int c4 = rl + j * LPR;
-      if (c4 < E4) pre[j] = Rows::load(d, ct, r, E, c4);
+      if (c4 < E4) pre[j] = Rows::load(row, c4);
     }
   }
   // n: the blocks from b + 1 on whose first look-up is in the segment (kBlock
@@ -455,7 +506,7 @@ __global__ __launch_bounds__(kBlock) void segment_fixup(
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
     const int c4 = rl + j * LPR;
-    if (c4 < E4) Rows::store(d, ct, r, E, c4, pre[j], acc[j], double(lr));
+    if (c4 < E4) Rows::store(row, c4, pre[j], acc[j], double(lr));
   }
 }
 
