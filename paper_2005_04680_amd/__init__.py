@@ -127,10 +127,22 @@ def check(code: int, where: str = "embbag") -> None:
 
 
 # ---- marshalling helpers ---------------------------------------------------
+@functools.lru_cache(maxsize=None)
+def _raw_stream():
+    """A function that gives the current stream's handle: torch's own raw
+    getter (0.3 us; torch.cuda.current_stream() builds a Stream object, 2.7 us),
+    or the public way where this torch has none."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    device = torch.cuda.current_device
+    return lambda: raw(device())
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _raw_stream()()
     return getattr(stream, "cuda_stream", stream)
 
 
@@ -163,21 +175,22 @@ def _need(ok, msg):
         raise ValueError(msg)
 
 
+# (The checks of every call format their message only when they fail.)
 def _check_bags(T, batch, offsets):
-    if offsets is not None and T >= 1 and batch >= 0:
-        _need(offsets.numel() == T * batch + 1,
-              f"offsets: {offsets.numel()} entries, expected num_tables * batch + 1 = "
-              f"{T * batch + 1}")
+    if offsets is not None and T >= 1 and batch >= 0 and offsets.numel() != T * batch + 1:
+        raise ValueError(f"offsets: {offsets.numel()} entries, expected num_tables * batch + 1 = "
+                         f"{T * batch + 1}")
 
 
 def _check_numel(t, n, name, exact=True):
-    if t is not None and n >= 0:
-        ok = t.numel() == n if exact else t.numel() >= n
-        _need(ok, f"{name}: {t.numel()} elements, expected {'' if exact else 'at least '}{n}")
+    if t is not None and n >= 0 and not (t.numel() == n if exact else t.numel() >= n):
+        raise ValueError(f"{name}: {t.numel()} elements, expected "
+                         f"{'' if exact else 'at least '}{n}")
 
 
 def _check_act(t, T, batch, dim, name):
-    if T >= 1 and batch >= 0:
+    if t is not None and T >= 1 and batch >= 0 and T * batch * dim >= 0 and \
+            t.numel() != T * batch * dim:
         _check_numel(t, T * batch * dim, f"{name} (num_tables x batch x dim)")
 
 
