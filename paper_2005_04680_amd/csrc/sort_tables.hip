@@ -20,11 +20,12 @@ namespace embbag {
 namespace {
 
 // Keys of one tile and its counts of the first digit; `vb` of the offsets.
+template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void table_keys(
     TableDesc d, const int32_t* __restrict__ I, const int32_t* __restrict__ O, int32_t NS,
     int32_t B, int32_t TB, int32_t vb, int32_t bits, uint64_t* __restrict__ out,
     uint16_t* __restrict__ hist, Tile* __restrict__ info, int32_t* __restrict__ status) {
-  __shared__ uint32_t lbag[kTile];
+  __shared__ uint32_t lbag[ITEMS * kThreads];
   __shared__ uint32_t lhist[1 << kMaxDigitBits];
   __shared__ int32_t krange[2];
   __shared__ int32_t lerr;
@@ -32,23 +33,23 @@ __global__ __launch_bounds__(kThreads) void table_keys(
   int err = 0;
   if (tid == 0) lerr = 0;
   lhist[tid] = 0;
-  const Tile me = find_tile(O, NS, d.num_tables, B, blk);
+  const Tile me = find_tile<ITEMS>(O, NS, d.num_tables, B, blk);
   if (tid == 0) info[blk] = me;
   const int start = me.start, count = me.count, t = me.table;
-  int32_t rv[kItems];
+  int32_t rv[ITEMS];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const int j = i * kThreads + tid;
     rv[i] = j < count ? I[start + j] : 0;
   }
   const int64_t k0 = int64_t(blk) * vb;
   if (bad_offsets(O, k0, min(k0 + vb, int64_t(TB)), NS, TB)) err = EMBBAG_ERR_OFFSETS;
   if (count > 0) {
-    if (fill_bags<false>(O, t * B, t * B + B - 1, start, count, NS, TB, lbag, krange))
+    if (fill_bags<ITEMS, false>(O, t * B, t * B + B - 1, start, count, NS, TB, lbag, krange))
       err = EMBBAG_ERR_OFFSETS;
     const uint32_t rows = d.rows[t], base = d.rowbase[t], mask = (1u << bits) - 1u;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
       const int j = i * kThreads + tid;
       if (j < count) {
         uint32_t r = uint32_t(rv[i]);
@@ -72,6 +73,7 @@ __global__ __launch_bounds__(kThreads) void table_keys(
 // A tile's counts of the digit at `shift`.  The keys arrive in the previous
 // pass's order, so equal digits often come in runs: the first lane of each run
 // in a wavefront adds the run's length.
+template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void table_counts(
     TableDesc d, const uint64_t* __restrict__ src, const Tile* __restrict__ info, int32_t shift,
     int32_t bits, uint16_t* __restrict__ hist) {
@@ -80,16 +82,16 @@ __global__ __launch_bounds__(kThreads) void table_counts(
   const Tile me = info[blk];
   if (me.count <= 0) return;
   lhist[tid] = 0;
-  uint32_t kv[kItems];
+  uint32_t kv[ITEMS];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const int j = i * kThreads + tid;
     kv[i] = j < me.count ? key_of(src[me.start + j]) : 0u;
   }
   __syncthreads();
   const uint32_t base = d.rowbase[me.table], R = 1u << bits;
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const uint32_t dg =
         i * kThreads + tid < me.count ? ((kv[i] - base) >> shift) & (R - 1u) : R;
     const uint32_t left = __shfl_up(dg, 1, kWave);
@@ -108,13 +110,14 @@ __global__ __launch_bounds__(kThreads) void table_counts(
 // sums the counts of its table's tiles by itself: R 16-bit counts a tile, two
 // to a word, the block's threads taking as many tiles at a time as they span.
 // FIRST: one more block folds the status words.
-template <bool VALS, bool FIRST>
-__global__ __launch_bounds__(kThreads) void table_scatter(
+template <int ITEMS, bool VALS, bool FIRST>
+__global__ __launch_bounds__(kThreads, ITEMS == 4 ? 8 : 4) void table_scatter(
     TableDesc d, const uint64_t* __restrict__ src, uint64_t* __restrict__ dst,
     const Tile* __restrict__ info, int32_t shift, int32_t bits,
     const uint16_t* __restrict__ hist, const float* __restrict__ vsrc, float* __restrict__ vdst,
     const int32_t* __restrict__ status, int32_t nblocks, int32_t* __restrict__ flags,
     int32_t* __restrict__ d_status, uint32_t token) {
+  constexpr int kTile = ITEMS * kThreads;
   __shared__ uint64_t buf[kTile];
   __shared__ float vbuf[VALS ? kTile : 1];
   __shared__ __align__(4) uint16_t whist[kWaves << kMaxDigitBits];
@@ -137,11 +140,11 @@ __global__ __launch_bounds__(kThreads) void table_scatter(
   const int count = me.count, R = 1 << bits;
   const int ipt = (count + kThreads - 1) / kThreads;
   const int j0 = w * (kWave * ipt) + lane;
-  uint64_t item[kItems];
-  float val[VALS ? kItems : 1];
-  bool valid[kItems];
+  uint64_t item[ITEMS];
+  float val[VALS ? ITEMS : 1];
+  bool valid[ITEMS];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const int j = j0 + i * kWave;
     valid[i] = i < ipt && j < count;
     item[i] = valid[i] ? src[me.start + j] : 0ull;
@@ -180,19 +183,19 @@ __global__ __launch_bounds__(kThreads) void table_scatter(
     if (p1) atomicAdd(&pre[2 * col + 1], p1);
   }
   const uint32_t base = d.rowbase[me.table];
-  uint32_t dig[kItems], rank[kItems];
+  uint32_t dig[ITEMS], rank[ITEMS];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) dig[i] = ((key_of(item[i]) - base) >> shift) & uint32_t(R - 1);
-  rank_digits(dig, valid, ipt, bits, whist, rank);
+  for (int i = 0; i < ITEMS; ++i) dig[i] = ((key_of(item[i]) - base) >> shift) & uint32_t(R - 1);
+  rank_digits<ITEMS>(dig, valid, ipt, bits, whist, rank);
   __syncthreads();
   const uint32_t mine_tot = tid < R ? tot[tid] : 0u;
   const uint32_t to = scan_block(mine_tot, scratch[0]) + (tid < R ? pre[tid] : 0u);
-  const uint32_t first = place_digits(bits, whist, scratch[1]);
+  const uint32_t first = place_digits<ITEMS == 2>(bits, whist, scratch[1]);
   __syncthreads();
   // (tot is free: it now holds a digit's place in the table less that in the tile)
   if (tid < R) tot[tid] = to - first;
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     if (valid[i]) {
       const uint32_t at = whist[(w << bits) + dig[i]] + rank[i];
       buf[at] = item[i];
@@ -210,18 +213,18 @@ __global__ __launch_bounds__(kThreads) void table_scatter(
   }
 }
 
-}  // namespace
+// Counts, tiles and status words of a sort, which share the histograms' place.
+size_t scratch_bytes(int64_t NS, int32_t T, int items, int bits) {
+  return size_t(tile_blocks(NS, T, items * kThreads)) *
+         ((sizeof(uint16_t) << bits) + sizeof(Tile) + sizeof(int32_t));
+}
 
-hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
-                              int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
-                              uint32_t token, const float* A, hipStream_t st) {
+template <int ITEMS>
+hipError_t sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
+                       int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
+                       uint32_t token, const float* A, int passes, int bits, hipStream_t st) {
   const int32_t TB = d.num_tables * B, ns = int32_t(NS);
-  uint32_t rows = 2;  // of the largest table: its bits decide the digits
-  for (int t = 0; t < d.num_tables; ++t) rows = d.rows[t] > rows ? d.rows[t] : rows;
-  const int nbits = 32 - __builtin_clz(rows - 1u);
-  const int passes = (nbits + kMaxDigitBits - 1) / kMaxDigitBits;
-  const int bits = (nbits + passes - 1) / passes;
-  const int blocks = tile_blocks(NS, d.num_tables);
+  const int blocks = tile_blocks(NS, d.num_tables, ITEMS * kThreads);
   const int32_t vb = (TB + blocks - 1) / blocks;
   uint16_t* hist = reinterpret_cast<uint16_t*>(ws + L.off_hist);
   Tile* info = reinterpret_cast<Tile*>(hist + (size_t(blocks) << bits));
@@ -233,15 +236,15 @@ hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, c
   float* vdst = reinterpret_cast<float*>(ws + (passes % 2 ? L.off_va : L.off_vb));
   float* vother = reinterpret_cast<float*>(ws + (passes % 2 ? L.off_vb : L.off_va));
   const float* vsrc = A;  // the first pass reads the caller's weights
-  hipLaunchKernelGGL(table_keys, dim3(blocks), dim3(kThreads), 0, st, d, I, O, ns, B, TB, vb, bits,
+  hipLaunchKernelGGL(table_keys<ITEMS>, dim3(blocks), dim3(kThreads), 0, st, d, I, O, ns, B, TB, vb, bits,
                      src, hist, info, status);
   for (int p = 0; p < passes; ++p) {
     const int shift = p * bits;
     if (p > 0)
-      hipLaunchKernelGGL(table_counts, dim3(blocks), dim3(kThreads), 0, st, d, src, info, shift,
+      hipLaunchKernelGGL(table_counts<ITEMS>, dim3(blocks), dim3(kThreads), 0, st, d, src, info, shift,
                          bits, hist);
 #define EMB_SCATTER(VALS, FIRST)                                                                 \
-  hipLaunchKernelGGL((table_scatter<VALS, FIRST>), dim3(blocks + (FIRST ? 1 : 0)),               \
+  hipLaunchKernelGGL((table_scatter<ITEMS, VALS, FIRST>), dim3(blocks + (FIRST ? 1 : 0)),               \
                      dim3(kThreads), 0, st, d, src, dst, info, shift, bits, hist, vsrc, vdst,    \
                      status, blocks, flags, d_status, token)
     if (A != nullptr && p == 0) EMB_SCATTER(true, true);
@@ -257,6 +260,28 @@ hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, c
     vother = const_cast<float*>(vsrc);
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const int32_t* O,
+                              int64_t NS, const BwdLayout& L, char* ws, int32_t* d_status,
+                              uint32_t token, const float* A, hipStream_t st) {
+  uint32_t rows = 2;  // of the largest table: its bits decide the digits
+  for (int t = 0; t < d.num_tables; ++t) rows = d.rows[t] > rows ? d.rows[t] : rows;
+  const int nbits = 32 - __builtin_clz(rows - 1u);
+  const int passes = (nbits + kMaxDigitBits - 1) / kMaxDigitBits;
+  const int bits = (nbits + passes - 1) / passes;
+  // Tiles of 2048 look-ups while they are at most a block per compute unit
+  // (524K 31 us instead of 33, 213K over 26 tables 27 instead of 32, 819K 47
+  // instead of 36) and their counts fit the workspace; tiles of 4096 then run
+  // two blocks to a compute unit (64 registers; 1.7M look-ups 64 us, 70 with
+  // one).
+  const size_t room = L.off_tot - L.off_hist;
+  if (NS <= int64_t(kNumCu) * 2 * kThreads && scratch_bytes(NS, d.num_tables, 2, bits) <= room)
+    return sort_tables<2>(d, B, I, O, NS, L, ws, d_status, token, A, passes, bits, st);
+  if (scratch_bytes(NS, d.num_tables, 4, bits) > room) return hipErrorInvalidValue;
+  return sort_tables<4>(d, B, I, O, NS, L, ws, d_status, token, A, passes, bits, st);
 }
 
 }  // namespace embbag

@@ -1,5 +1,5 @@
 // Tiles of one table's look-ups, as the sorts that work table by table cut
-// them: a block of kThreads threads per tile, kItems keys per thread.
+// them: a block of kThreads threads per tile, ITEMS keys per thread.
 #pragma once
 
 #include "common.hpp"
@@ -9,8 +9,6 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kTile = 4096;
-constexpr int kItems = kTile / kThreads;
 constexpr int kMaxDigitBits = 10;  // one digit value per thread
 
 // One tile, as the first kernel of a sort leaves it for the next ones.
@@ -22,7 +20,7 @@ struct Tile {
 };
 
 // Blocks that cover every table's tiles: each table's last may be part full.
-inline int tile_blocks(int64_t NS, int32_t T) { return int((NS + kTile - 1) / kTile) + T; }
+inline int tile_blocks(int64_t NS, int32_t T, int tile) { return int((NS + tile - 1) / tile) + T; }
 
 // Inclusive scan over a wavefront by lane moves inside the vector unit: shifts
 // by 1, 2, 4 and 8 within rows of 16 lanes, then each row's last value to the
@@ -60,8 +58,10 @@ __device__ __forceinline__ void publish(int32_t err, uint32_t token, int32_t* fl
 // wavefront finds it for itself from the T + 1 offsets at the tables' edges,
 // one per lane, forced into 0 .. NS and increasing order: offsets that are not
 // are reported by check_offsets, and the tiles still cover the list once.
+template <int ITEMS>
 __device__ __forceinline__ Tile find_tile(const int32_t* O, int32_t NS, int32_t T, int32_t B,
                                           int blk) {
+  constexpr int kTile = ITEMS * kThreads;
   const int lane = lane_id();
   int edge = lane < T ? min(max(O[int64_t(lane) * B], 0), NS) : NS;
   if (lane == 0) edge = 0;
@@ -120,14 +120,14 @@ __device__ __forceinline__ bool bad_offsets(const int32_t* O, int64_t k0, int64_
 // inside [lo, hi] and the look-ups inside the tile.  Every thread calls it;
 // with CHECK the offsets of [lo, hi], which is then taken whole, are checked.
 // Ends with a barrier.
-template <bool CHECK>
+template <int ITEMS, bool CHECK>
 __device__ __forceinline__ bool fill_bags(const int32_t* O, int lo, int hi, int start, int count,
                                           int32_t NS, int32_t TB, uint32_t* lbag,
                                           int32_t* krange) {
   constexpr int Q = kOffsetsAtOnce;
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
   bool bad = false;
-  for (int i = tid; i < kTile; i += kThreads) lbag[i] = 0;
+  for (int i = tid; i < ITEMS * kThreads; i += kThreads) lbag[i] = 0;
   const bool known = CHECK || hi - lo < 2 * kThreads;
   if (!known && w < 2) {
     const int x = w == 0 ? start : start + count - 1;
@@ -174,21 +174,22 @@ __device__ __forceinline__ bool fill_bags(const int32_t* O, int lo, int hi, int 
 // holds keys [w * 64 * ipt, (w + 1) * 64 * ipt), item i of lane l being key
 // w * 64 * ipt + i * 64 + l: ranked item by item they keep their order.
 // hist[w * R + digit], zero before, counts the wavefront's keys of a digit.
+template <int ITEMS>
 __device__ __forceinline__ void rank_digits(const uint32_t* dig, const bool* valid, int ipt,
                                             int bits, uint16_t* hist, uint32_t* rank) {
   const int lane = lane_id(), row = wave_id() << bits;
   const uint64_t below = (1ull << lane) - 1ull;
   // Lanes whose digit is this lane's: one ballot per bit, every item's at once.
-  uint32_t plo[kItems], phi[kItems];
+  uint32_t plo[ITEMS], phi[ITEMS];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     const uint64_t all = __builtin_amdgcn_ballot_w64(valid[i]);
     plo[i] = uint32_t(all);
     phi[i] = uint32_t(all >> 32);
   }
   for (int b = 0; b < bits; ++b) {
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
       if (i < ipt) {
         // keep the lanes whose bit b is this lane's (a & ~(b ^ c) per half)
         const int32_t sb = __builtin_amdgcn_sbfe(int32_t(dig[i]), b, 1);  // 0 or -1
@@ -199,7 +200,7 @@ __device__ __forceinline__ void rank_digits(const uint32_t* dig, const bool* val
     }
   }
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     if (i < ipt) {
       const uint64_t peers = (uint64_t(phi[i]) << 32) | plo[i];
       const uint32_t lrank = uint32_t(__popcll(peers & below));
@@ -212,23 +213,36 @@ __device__ __forceinline__ void rank_digits(const uint32_t* dig, const bool* val
 
 // From the wavefronts' counts (after a barrier) to each wavefront's first
 // place for a digit among the sorted tile; returns the thread's own digit's
-// first place (digit tid < 1 << bits).  A barrier must follow.
+// first place (digit tid < 1 << bits).  A barrier must follow.  KEEP holds the
+// counts in registers meanwhile, which saves 16 LDS reads (0.3 us a pass) where
+// a second block of the compute unit does not need the registers.
+template <bool KEEP>
 __device__ __forceinline__ uint32_t place_digits(int bits, uint16_t* hist, uint32_t* scratch) {
   const int tid = threadIdx.x, R = 1 << bits;
   uint32_t c[kWaves], run = 0;
   if (tid < R) {
 #pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) c[ww] = hist[(ww << bits) + tid];
-#pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) run += c[ww];
+    for (int ww = 0; ww < kWaves; ++ww) {
+      c[ww] = hist[(ww << bits) + tid];
+      run += c[ww];
+    }
   }
   const uint32_t first = scan_block(run, scratch);
   if (tid < R) {
     uint32_t ex = first;
+    if constexpr (KEEP) {
 #pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) {
-      hist[(ww << bits) + tid] = uint16_t(ex);
-      ex += c[ww];
+      for (int ww = 0; ww < kWaves; ++ww) {
+        hist[(ww << bits) + tid] = uint16_t(ex);
+        ex += c[ww];
+      }
+    } else {
+#pragma unroll 4
+      for (int ww = 0; ww < kWaves; ++ww) {
+        const uint32_t n = hist[(ww << bits) + tid];
+        hist[(ww << bits) + tid] = uint16_t(ex);
+        ex += n;
+      }
     }
   }
   return first;

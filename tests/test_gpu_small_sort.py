@@ -1,6 +1,6 @@
 """Small calls sort tile by tile in LDS, mid-sized ones table by table: the sorted (key, bag) words, unique
 keys and segment offsets must be those of a stable sort, bit for bit, at the
-edges of tiles (4096 look-ups of a table), of the one-block form (4096 in all)
+edges of tiles (2048 or 4096 look-ups of a table), of the one-block form (4096 in all)
 and of the path's range; data errors are reported as by the radix sort.
 """
 import numpy as np
@@ -55,6 +55,10 @@ CASES = {
     "more bags than a block's threads": ((70000, 800), 9000, (12289, 5000)),
     "last size of the path": ((200000,) * 4, 3000, (30000, 30000, 30000, 8304)),
     "first size past it": ((200000,) * 4, 3000, (30000, 30000, 30000, 8305)),
+    "small, tiles of 4096": ((200000, 1 << 21, 300), 800, (27000, 40960, 8193)),
+    "by table, 64 tables of 20 bits": ((1 << 20,) * 64, 40, (1536,) * 63 + (1600,)),
+    "by table, last of 2048": ((90000, 5, 1 << 20), 20000, (262144, 2049, 260095)),
+    "by table, first of 4096": ((90000, 5, 1 << 20), 20000, (262144, 2049, 260096)),
     "by table, one row each": ((1, 1), 700, (60000, 40000)),
     "by table, one pass": ((1000, 3, 1024), 9000, (40960, 4097, 90000)),
     "by table, two passes": ((1 << 20, 700, 5), 50, (0, 100000, 4096)),
@@ -108,7 +112,8 @@ def test_data_errors(counts):
     assert rc == 0 and status == 0
 
 
-@pytest.mark.parametrize("counts", [(2000, 1500), (9000, 4097), (50000, 70000)])
+@pytest.mark.parametrize("counts", [(2000, 1500), (9000, 4097), (30000, 4097), (50000, 70000),
+                                    (300000, 230000)])
 def test_weights_travel_with_the_look_ups(counts):
     rows, batch, dim = (900, 40000), 77, 12
     rng = np.random.default_rng(5)
