@@ -52,19 +52,22 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
   return (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
 }
 
-// Row groups that walk several bags are held to 6 waves per SIMD (80 VGPRs)
-// for one float4 group per lane and plain sums, 5 for weighted or mean
-// pooling (their coefficients take registers); wider rows take what they need.
+// Row groups that walk several bags keep 4 rows in flight and are held to 8
+// waves per SIMD (64 VGPRs) for one float4 group per lane and plain sums, 6 for
+// weighted or mean pooling (their coefficients take registers): short bags are
+// latency, which waves hide better than loads (against 8 rows at 6 waves:
+// 66K bags of 5, E = 64 17.1 -> 14.8 us, E = 128 24.4 -> 22.3).  Wider rows take
+// what they need.
 template <int LPR, int CPL, bool SPLIT, bool MULTI, int MODE, bool YBF16>
-__global__ __launch_bounds__(kBlock, MULTI ? (CPL == 1 && MODE == kPoolPlain ? 6 : (CPL == 1 ? 5 : 1)) : 1) void fwd_gather_sum(
+__global__ __launch_bounds__(kBlock, MULTI && CPL == 1 ? (MODE == kPoolPlain ? 8 : 6) : 1) void fwd_gather_sum(
     TableDesc d, const int32_t* __restrict__ I, const int32_t* __restrict__ O, int32_t NS,
     int32_t B, int32_t G, int32_t groups_per_table, int32_t items, void* __restrict__ Y,
     int32_t* __restrict__ status, const float* __restrict__ A, int32_t in_order) {
   constexpr int R = kWave / LPR;
   // Row loads in flight per lane: 10 when a wavefront reads one 1 KB row per
   // load and walks one bag (58 VGPRs, still 8 waves per SIMD); fewer as the
-  // rows per lane grow.
-  constexpr int U = CPL == 1 ? (LPR == kWave && !MULTI ? 10 : 8) : (CPL == 2 ? 4 : 2);
+  // rows per lane grow, or where a row group walks several bags.
+  constexpr int U = CPL == 1 ? (MULTI ? 4 : (LPR == kWave ? 10 : 8)) : (CPL == 2 ? 4 : 2);
   const int E = d.dim;
   const int E4 = E / 4;
   const int lane = lane_id();
@@ -128,15 +131,16 @@ __global__ __launch_bounds__(kBlock, MULTI ? (CPL == 1 && MODE == kPoolPlain ? 6
   if constexpr (MULTI) {
     const bool one = !olanes ? false : !bad && (rl > k1 - k0 || ov == s0 + rl);
     if (__builtin_amdgcn_ballot_w64(!one) == 0ull) {
+      constexpr int UC = CPL == 1 ? 8 : U;  // rows in flight per lane
       const int n = k1 - k0;
       const int mine = rl < n ? I[s0 + rl] : 0;
       float aw = 1.f;
       if constexpr (MODE == kPoolWeighted) aw = rl < n ? A[s0 + rl] : 0.f;
-      for (int i = 0; i < G; i += U) {
-        f4 v[U][CPL];
-        bool ok[U];
+      for (int i = 0; i < G; i += UC) {
+        f4 v[UC][CPL];
+        bool ok[UC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < UC; ++u) {
           const int from = min(i + u, n - 1);
           const int idx = __shfl(mine, rg * LPR + from, kWave);
           ok[u] = uint32_t(idx) < M;
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(kBlock, MULTI ? (CPL == 1 && MODE == kPoolPlain ? 6
             v[u][j] = load_row4<SPLIT>(base, ok[u] ? uint32_t(idx) : 0u, E, min(rl + j * LPR, E4 - 1));
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < UC; ++u) {
           if (i + u >= n) break;
           d4 one_row[CPL];
           double c = 1.0;
@@ -345,7 +349,7 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
     return hipGetLastError();
   }
   // Bags per row group.  A wavefront's loads go out once per group of bags
-  // (offsets, look-ups, rows), so short bags share a group: 16 bags of one
+  // (offsets, look-ups, rows), so short bags share a group: 8 bags of one
   // look-up, 8 look-ups' worth of longer ones (of 3 look-ups, E = 64, 213K
   // bags: 8 37 us, 16 42; of 8, E = 16, 66K bags: 7 and 14).  Groups shrink
   // while the grid has fewer than kFillBlocks blocks (66K bags of 0 to 3,
@@ -356,7 +360,7 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
   const int per_block = kWavesPerBlock * (kWave / g.lpr);
   constexpr int64_t kFillBlocks = 1024;
   const int64_t avg = NS / TB;
-  int G = avg <= 1 ? 16 : (avg < 8 ? int(8 / avg) : 1);
+  int G = avg <= 1 ? 8 : (avg < 8 ? int(8 / avg) : 1);
   if (g.lpr >= 4 && G >= g.lpr) G = g.lpr / 2;
   G = G > B ? B : G;
   const int least = avg <= 1 ? 4 : 1;
