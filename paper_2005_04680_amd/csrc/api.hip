@@ -174,11 +174,11 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   // of three, in four launches instead of nine.  A block of the scatter adds up
   // the counts of its table's tiles by itself, so that the work grows with the
   // square of the tiles per table.  Measured, us per prepare, whole list / by
-  // table: 120K look-ups over 2 tables 33.9 / 27.2; 300K over 40 42.2 / 31.2;
-  // 524K over 8 (16 tiles each) 43.9 / 32.6; 819K over 8 54.4 / 35.8; 525K
-  // weighted over 5 of 3M rows 52.2 / 42.6; 1.7M over 26 73.9 / 70.5; 400K in
-  // one table (98 tiles) 45.4 / 44.4; 1M in one (244) 44.6 / 60.7; 2M over 8
-  // 69.1 / 70.5; 13.1M over 16 253 / 372.
+  // table: 120K look-ups over 2 tables 33.9 / 25.2; 300K over 40 42.2 / 27.5;
+  // 524K over 8 (16 tiles of 4096 each) 43.9 / 30.7; 819K over 8 54.4 / 36.8;
+  // 525K weighted over 5 of 3M rows 52.2 / 42.9; 1.7M over 26 73.9 / 63.7; 2M
+  // over 8 69.2 / 63.6; 400K in one table (98 tiles) 45.5 / 48.7; 1M in one (244)
+  // 44.6 / 61.4; 13.1M over 16 (200 each) 253 / 275.
   L.by_table = !L.small && NS > 0 && NS <= kTableSort && NS <= int64_t(T) * kTableSortPerTable &&
                int64_t(T) * B <= 2 * NS;
   L.sorted_in_b = !L.small && !L.by_table && NS > 0 && L.passes % 2 == 1;
@@ -200,13 +200,18 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   const int64_t vblocks = (int64_t(T) * B + 1 + kOffsetsPerBlock - 1) / kOffsetsPerBlock;
   L.nkeyblocks = L.ntiles > vblocks ? L.ntiles : vblocks;
   if (L.nkeyblocks < 1) L.nkeyblocks = 1;
-  // Chunks of the segmented reduce (one per row group): 8 look-ups, doubled
-  // while kReduceBlocks blocks remain, up to 256.  The chip holds 1024 to 1280
-  // blocks at once; measured at 1024 / 2048 / 4096 / 8192 blocks, us per
-  // update: 1.7M look-ups of E = 128 264 / 225 / 219 / 220, 525K weighted of
-  // E = 100 82 / 74 / 75 / 84, 1.8M of E = 64 100 / 91 / 95 / 108, 524K of
-  // E = 64 40 / 43 / 43 / 44.  Beyond 256 long walks lose what fewer block
-  // boundaries gain (13.1M of E = 256: 64 1760, 128 1705, 256 1694, 512 1743).
+  // Chunks of the segmented reduce, one per row group: a multiple of the
+  // look-ups that a walk keeps in flight, 8 to 256.  The chip holds
+  // kReduceBlocks blocks at once.  A call of 16-lane and wider rows that fits
+  // them with chunks of up to 32 runs as one round of blocks, all others as
+  // four.  Measured with 1 / 2 / 4 / 8 rounds, us per update: 524K look-ups of
+  // E = 64 (chunks of 32 in one round) 39.3 / 41.9 / 44.4 / 44.4, 400K in one
+  // table (28) 31.4 / 36.1 / 41.6 / 41.6; 540K weighted of E = 100 (72) 72.1 /
+  // 72.8 / 70.9 / 72.0, 1.7M of E = 128 (208) 245 / 247 / 220 / 217, 1.8M of E =
+  // 64 88.9 / 90.3 / 92.8 / 97.3, 4.4M of E = 16 100.1 / 97.7 / 95.4 / 94.6, 2M of
+  // E = 16 (32, 16 row groups a wavefront) 64.8 / 57.8 / 55.7 / 55.6.  Beyond 256
+  // long walks lose what fewer block boundaries gain (13.1M of E = 256: 64 1760,
+  // 128 1705, 256 1694, 512 1743).
   const RowGeom g = row_geom(E);
   const int64_t groups = kBlock / g.lpr;
   // Look-ups per pair of carry slots that the workspace has room for; a block
@@ -215,8 +220,15 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   int64_t room = 128 / rgw > 8 ? 128 / rgw : 8;
   while (room < 1024 && room * 2 * 32768 * rgw <= NS) room *= 2;
   const int64_t slots = (NS + room - 1) / room;
-  int64_t c = 8;
-  while (c < 256 && (c * groups < room || c * 2 * groups * kReduceBlocks <= NS)) c *= 2;
+  const int64_t unit = g.lpr == kWave ? 8 : 4;
+  auto chunk = [&](int64_t rounds) {
+    const int64_t per = groups * kReduceBlocks * rounds * unit;
+    return (NS + per - 1) / per * unit;
+  };
+  int64_t c = chunk(1);
+  if (c > 32 || g.lpr < 16) c = chunk(4);
+  const int64_t least = room / groups > 8 ? room / groups : 8;
+  c = c < least ? least : (c > 256 ? 256 : c);
   L.chunk = c;
   L.nchunks = (NS + c - 1) / c;
   L.nblocks = (NS + c * groups - 1) / (c * groups);

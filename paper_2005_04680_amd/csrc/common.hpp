@@ -22,7 +22,7 @@ constexpr int64_t kMallBytes = int64_t(256) << 20;  // Infinity Cache (MALL)
 constexpr int kMaxRadixBits = 10;
 constexpr int kMaxRadix = 1 << kMaxRadixBits;
 constexpr int kMaxItemsPerThread = 16;  // radix tile: kBlock * (4, 8 or 16) keys
-constexpr int kReduceBlocks = 2048;  // blocks that the segmented reduce is cut into, at least
+constexpr int kReduceBlocks = kNumCu * 4;  // blocks of the segmented reduce that run at once
 constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block validates, at most
 
 // Which calls are sorted table by table, in tiles of 4096 look-ups (see
@@ -30,7 +30,7 @@ constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block valida
 constexpr int kSmallSort = 24 * 4096;
 constexpr int kSmallPerTable = 8 * 4096;
 constexpr int kSmallOffsets = 32768;
-constexpr int64_t kTableSort = 448 * 4096;
+constexpr int64_t kTableSort = 512 * 4096;
 constexpr int64_t kTableSortPerTable = 64 * 4096;
 
 // Sentinel for "no key": keys are < 2^31 because sum(M_t) < 2^31.
