@@ -162,7 +162,10 @@ __device__ __forceinline__ bool fill_bags(const int32_t* O, int lo, int hi, int 
       const int64_t k = q0 + q * stride;
       if (k >= nb) break;
       if constexpr (CHECK) bad = bad || bad_offset(k, oa[q], ob[q], NS, TB);
-      const int a = max(oa[q], start) - start, b = min(ob[q], start + count) - start;
+      // (both ends forced into the tile before they are moved: a bad offset may
+      // be any int)
+      const int a = min(max(oa[q], start), start + count) - start;
+      const int b = min(max(ob[q], start), start + count) - start;
       for (int s = a + lead; s < b; s += share) lbag[s] = uint32_t(k0 + k);
     }
   }

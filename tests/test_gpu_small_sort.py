@@ -87,7 +87,8 @@ def test_sorted_as_by_a_stable_sort(name, hot):
     assert np.array_equal(got["seg_off"], seg)
 
 
-@pytest.mark.parametrize("counts", [(3000, 1000), (9000, 4000), (70000, 60000)])
+@pytest.mark.parametrize("counts", [(3000, 1000), (9000, 4000), (70000, 60000),
+                                    (400000, 200000)])
 def test_data_errors(counts):
     rows, batch = (500, 800), 300
     rng = np.random.default_rng(3)
@@ -102,7 +103,11 @@ def test_data_errors(counts):
     short[-1] -= 1
     edge = O.copy()
     edge[batch] = 2 ** 31 - 1
-    for idx, off, code in ((bad_row, O, pk.EMBBAG_ERR_INDEX_RANGE),
+    low, high = O.copy(), O.copy()
+    low[batch + 9:batch + 12] = -2 ** 31
+    high[20:23] = 2 ** 31 - 1
+    for idx, off, code in ((I, low, pk.EMBBAG_ERR_OFFSETS), (I, high, pk.EMBBAG_ERR_OFFSETS),
+                           (bad_row, O, pk.EMBBAG_ERR_INDEX_RANGE),
                            (negative, O, pk.EMBBAG_ERR_INDEX_RANGE),
                            (I, down, pk.EMBBAG_ERR_OFFSETS), (I, short, pk.EMBBAG_ERR_OFFSETS),
                            (bad_row, edge, pk.EMBBAG_ERR_OFFSETS)):
