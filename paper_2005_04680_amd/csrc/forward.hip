@@ -350,21 +350,21 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
   }
   // Bags per row group.  A wavefront's loads go out once per group of bags
   // (offsets, look-ups, rows), so short bags share a group: 8 bags of one
-  // look-up, 8 look-ups' worth of longer ones (of 3 look-ups, E = 64, 213K
-  // bags: 8 37 us, 16 42; of 8, E = 16, 66K bags: 7 and 14).  Groups shrink
-  // while the grid has fewer than kFillBlocks blocks (66K bags of 0 to 3,
-  // E = 64: 1024 blocks 11.6 us, 512 14.5), but bags of one look-up stay four
-  // to a group, where they are copied (13K bags of E = 128: four 4.6 us, two
-  // 5.2, one 6.7), and a group's offsets have to fit its lanes.
+  // look-up, 16 look-ups' worth of longer ones (920K bags of 3, E = 40: 16 98
+  // us, 8 104).  Groups shrink while the grid has fewer than `fill` blocks (66K
+  // bags of 1 to 9, E = 64: 2048 blocks 15 us, 1024 17; 66K of 0 to 3: 1024 blocks
+  // 11.6, 512 14.5), but bags of one look-up stay four to a group, where they
+  // are copied (13K bags of E = 128: four 4.6 us, two 5.2, one 6.7), and a
+  // group's offsets have to fit its lanes.
   const RowGeom g = row_geom(d.dim);
   const int per_block = kWavesPerBlock * (kWave / g.lpr);
-  constexpr int64_t kFillBlocks = 1024;
   const int64_t avg = NS / TB;
-  int G = avg <= 1 ? 8 : (avg < 8 ? int(8 / avg) : 1);
+  int G = avg <= 1 ? 8 : (avg < 16 ? int(16 / avg) : 1);
   if (g.lpr >= 4 && G >= g.lpr) G = g.lpr / 2;
   G = G > B ? B : G;
   const int least = avg <= 1 ? 4 : 1;
-  while (G > least && TB < kFillBlocks * per_block * G) G /= 2;
+  const int64_t fill = avg <= 1 ? 1024 : 2048;
+  while (G > least && TB < fill * per_block * G) G /= 2;
   const int gpt = (B + G - 1) / G;
   const int64_t items = int64_t(d.num_tables) * gpt;
   // Blocks of one wavefront where four would leave compute units idle (128
