@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kBlock, MULTI && CPL == 1 ? (MODE == kPoolPlain ? 8
           const int from = min(i + u, n - 1);
           const int idx = __shfl(mine, rg * LPR + from, kWave);
           ok[u] = uint32_t(idx) < M;
-          if (!ok[u]) err = EMBBAG_ERR_INDEX_RANGE;
+          if (!ok[u]) err = min(err, EMBBAG_ERR_INDEX_RANGE);
 #pragma unroll
           for (int j = 0; j < CPL; ++j)
             v[u][j] = load_row4<SPLIT>(base, ok[u] ? uint32_t(idx) : 0u, E, min(rl + j * LPR, E4 - 1));

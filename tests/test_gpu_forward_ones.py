@@ -71,3 +71,17 @@ def test_index_out_of_range(bad):
     gt = GpuTables([np.ones((7, 128), np.float32)] * 3)
     rc, _ = gt.forward(700, I, O)
     assert rc == 0 and gt.read_status() == pk.EMBBAG_ERR_INDEX_RANGE
+
+
+@pytest.mark.parametrize("dim", [32, 128, 512])
+@pytest.mark.parametrize("shift,bad_at", [(1, 3), (0, -4)])
+def test_bad_offsets_win_over_a_bad_index(dim, shift, bad_at):
+    """One look-up in every bag, but the list starts at 1 (or ends before
+    num_indices), and a group of bags that sees this also reads a bad index."""
+    T, batch = 3, 700
+    O = np.arange(T * batch + 1, dtype=np.int32) + shift
+    I = np.zeros(T * batch + 1, np.int32)  # one look-up more than the bags hold
+    I[bad_at] = 7
+    gt = GpuTables([np.ones((7, dim), np.float32)] * T)
+    rc, _ = gt.forward(batch, I, O)
+    assert rc == 0 and gt.read_status() == pk.EMBBAG_ERR_OFFSETS
