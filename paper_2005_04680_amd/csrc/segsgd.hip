@@ -12,7 +12,8 @@
 // row in registers and, after the block's one barrier, adds the sums that the
 // following row groups parked in LDS.  A segment that crosses blocks leaves
 // two sums in global memory (slot 2b: block b's part of a segment begun before
-// it, slot 2b+1: of one going on past it) and is applied by a second kernel.
+// it, slot 2b+1: of one going on past it) and is applied by a second kernel;
+// where it may cross very many, a kernel between them adds up groups of blocks.
 // Every touched row is read and written exactly once, and its sum is taken in
 // an order that positions alone decide (the result is bit-reproducible).
 //
@@ -411,34 +412,94 @@ __global__ __launch_bounds__(kBlock) void segment_sgd(
   }
 }
 
-// Segments that cross block boundaries: one block per boundary.  It has work
-// if the segment at the boundary begins in the block before it; the segment's
+// Sums over kPre blocks that one segment fills, for segments over very many
+// blocks: a fix-up block reads partial sums at one compute unit's 150 GB/s, and
+// 4096 of E = 256 are 8 MB.  The sum of an aligned group of kPre blocks from b0 on
+// goes to slot 2 * b0 + 1 (a block that a segment fills has no use for it); the
+// fix-up knows from the segment's ends alone which groups are full.
+constexpr int kPre = 16;
+
+template <int LPR, int CPL>
+__global__ __launch_bounds__(kBlock) void segment_presum(
+    const uint64_t* __restrict__ sorted, uint32_t span, int32_t nblocks, int32_t E,
+    double* __restrict__ carry, const int32_t* __restrict__ flags, uint32_t token) {
+  constexpr int R = kWave / LPR;
+  constexpr int GU = CPL == 1 ? kPre : (CPL == 2 ? kPre / 2 : kPre / 4);
+  const int lane = lane_id(), rg = lane / LPR, rl = lane % LPR;
+  const int b0 = ((int(blockIdx.x) * kWavesPerBlock + wave_id()) * R + rg + 1) * kPre;
+  if (b0 + kPre >= nblocks) return;  // the look-up after the group has to be in the segment
+  const uint32_t first = uint32_t(b0) * span, after = first + kPre * span;
+  const uint32_t kf = key_of(sorted[first - 1]), ka = key_of(sorted[after]);
+  if (flags[0] != 0 || uint32_t(flags[1]) != token || kf != ka) return;
+  d4 acc[CPL];
+#pragma unroll
+  for (int j = 0; j < CPL; ++j) acc[j] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int u0 = 0; u0 < kPre; u0 += GU) {
+    d4 v[GU][CPL];
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        const int c4 = rl + j * LPR;
+        v[u][j] = c4 < E / 4 ? *reinterpret_cast<const d4*>(carry + 2 * int64_t(b0 + u0 + u) * E + c4 * 4)
+                             : d4{0.0, 0.0, 0.0, 0.0};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) acc[j] += v[u][j];
+    }
+  }
+  store_carry<CPL>(carry, 2 * int64_t(b0) + 1, E, rl, LPR, acc);
+}
+
+// Threads of a fix-up block.  kBlock of them look after one boundary; a segment
+// over many blocks is the work of all, so that one row's partial sums are not a
+// long chain of loads.  Narrow rows have row groups enough in kBlock threads,
+// and more than 2 float4 groups per lane take registers that 1024 threads have not.
+template <int LPR, int CPL>
+constexpr int kFixThreads = LPR < 32 ? kBlock : (CPL == 1 ? 4 * kBlock : 2 * kBlock);
+
+// Segments that cross block boundaries: kBlock threads per boundary.  They have
+// work if the segment at the boundary begins in the block before it; the segment's
 // partial sums are that block's slot 2b+1 and the first slots of the `n`
 // blocks that follow and begin inside it.  Row group g adds those of blocks
 // g, g + NG, ... in order, and row group 0 adds the row groups' sums in order
-// and applies the row once: the order depends on the positions alone.
+// and applies the row once.  Where n is large (at most one of a fix-up block's
+// boundaries can be: the segment covers the others) the row groups of the whole
+// fix-up block add them so.  The order depends on the positions alone.
+// Measured, us per update of 500K look-ups, all of one row / of many rows, with
+// row groups of kBlock threads and 4 loads in flight alone: E = 64 34 / 29, E = 128
+// 182 / 58, E = 256 196 / 89; so: 26 / 29, 72 / 52, 52 / 86.  64 registers where the
+// row groups are few: blocks of 1024 threads then share a compute unit by twos.
 template <int LPR, int CPL, class Rows>
-__global__ __launch_bounds__(kBlock) void segment_fixup(
+__global__ __launch_bounds__((kFixThreads<LPR, CPL>), CPL == 1 && LPR >= 32 ? 8 : 1) void segment_fixup(
     TableDesc d, const uint64_t* __restrict__ sorted, int32_t NS, uint32_t span, int32_t nblocks,
     int32_t B, float inv_b, float lr, const double* __restrict__ carry,
-    const int32_t* __restrict__ flags, uint32_t token) {
+    const int32_t* __restrict__ flags, uint32_t token, bool presummed) {
   constexpr int NG = kGroups<LPR>;
   constexpr int R = kWave / LPR;
-  __shared__ d4 part[NG * LPR * CPL];
-  __shared__ int32_t counts[kWavesPerBlock];
-  const int b = int(blockIdx.x);
-  const uint32_t lo = uint32_t(b) * span, hi = lo + span;  // hi < NS (host)
-  const uint64_t wl = sorted[hi - 1], wn = sorted[hi];
-  const uint64_t wb = lo > 0 ? sorted[lo - 1] : ~0ull;
-  const uint32_t kl = key_of(wl);
-  if (flags[0] != 0 || uint32_t(flags[1]) != token) return;
-  if (key_of(wn) != kl || key_of(wb) == kl) return;
-  const int E = d.dim, E4 = E / 4;
-  const int tid = threadIdx.x, lane = lane_id();
+  constexpr int Q = kFixThreads<LPR, CPL> / kBlock;  // boundaries of the fix-up block
+  constexpr int UF = CPL == 1 ? (LPR < 32 ? 8 : 4) : (CPL == 2 ? 4 : 2);
+  // partials per row group up to which a boundary's own row groups add them
+  constexpr int US = CPL == 1 ? 4 : (CPL == 2 ? 2 : 1);
+  static_assert(US * NG >= Q, "a long segment must cover the fix-up block's other boundaries");
+  __shared__ d4 part[Q * NG * LPR * CPL];
+  __shared__ int32_t many[Q];  // blocks of the boundary's segment if they are many
+  const int lane = lane_id(), wave = wave_id();
   const int rg = lane / LPR, rl = lane % LPR;
-  const int grp = wave_id() * R + rg;
-  // The partial that row group g adds first, requested before it is known
-  // whether its block belongs to the segment.
+  const int q = wave / kWavesPerBlock, grp = wave % kWavesPerBlock * R + rg;
+  const int b = int(blockIdx.x) * Q + q;
+  // The words at the boundary, requested with the flags.
+  const bool real = b + 1 < nblocks;
+  const uint32_t lo = uint32_t(b) * span, hi = lo + span;  // hi < NS where real
+  const uint64_t wl = real ? sorted[hi - 1] : 0ull, wn = real ? sorted[hi] : ~0ull;
+  const uint64_t wb = real && lo > 0 ? sorted[lo - 1] : ~0ull;
+  if (flags[0] != 0 || uint32_t(flags[1]) != token) return;
+  const int E = d.dim, E4 = E / 4;
+  const uint32_t kl = key_of(wl);
   auto slot = [&](int64_t s, d4* v) {
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
@@ -446,68 +507,120 @@ __global__ __launch_bounds__(kBlock) void segment_fixup(
       v[j] = c4 < E4 ? *reinterpret_cast<const d4*>(carry + s * E + c4 * 4) : d4{0.0, 0.0, 0.0, 0.0};
     }
   };
-  d4 first[CPL], acc[CPL];
-  if (b + 1 + grp < nblocks) slot(2 * int64_t(b + 1 + grp), first);
-  const int ct = table_of_bag(bag_of(wl), B, inv_b);
-  const typename Rows::Row row = Rows::row(Rows::table(d, ct), kl - d.rowbase[ct], E);
+  d4 acc[CPL];
+  typename Rows::Row row;
   typename Rows::Pre pre[CPL];
-  if (grp == 0) {
-    slot(2 * int64_t(b) + 1, acc);
+  auto add_and_apply = [&](const d4* sums, int m) {
+#pragma unroll 4
+    for (int k = 0; k < m; ++k) {
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) acc[j] += sums[(k * CPL + j) * LPR + rl];
+    }
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
       const int c4 = rl + j * LPR;
-      if (c4 < E4) pre[j] = Rows::load(row, c4);
+      if (c4 < E4) Rows::store(row, c4, pre[j], acc[j], double(lr));
+    }
+  };
+  d4* own = part + q * (NG * LPR * CPL);
+  int n = 0;  // the same in every lane of the boundary's wavefronts
+  if (key_of(wn) == kl && key_of(wb) != kl) {  // (keys are below 2^31)
+    // The partial that row group g adds first, requested before it is known
+    // whether its block belongs to the segment.
+    d4 sum[CPL];
+    if (b + 1 + grp < nblocks) slot(2 * int64_t(b + 1 + grp), sum);
+    if (grp == 0) {
+      const int ct = table_of_bag(bag_of(wl), B, inv_b);
+      row = Rows::row(Rows::table(d, ct), kl - d.rowbase[ct], E);
+      slot(2 * int64_t(b) + 1, acc);
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        const int c4 = rl + j * LPR;
+        if (c4 < E4) pre[j] = Rows::load(row, c4);
+      }
+    }
+    // n: the blocks from b + 1 on whose first look-up is in the segment (the
+    // keys are sorted, so they come first): a look at 64 of them, and if all
+    // are, a 64-way search for the last one.
+    auto in = [&](int64_t c) {
+      return c < nblocks && key_of(sorted[uint32_t(c) * span]) == kl;
+    };
+    const uint64_t near = __builtin_amdgcn_ballot_w64(in(int64_t(b) + 1 + lane));
+    n = __popcll(near);
+    if (n == kWave) {
+      int first = b + kWave, last = nblocks - 1;  // block `first` is in the segment
+      while (first < last) {
+        const int step = int((int64_t(last) - first + kWave) / kWave);
+        const int64_t c = first + int64_t(lane) * step;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(c <= last && in(c));
+        first += (63 - __builtin_clzll(m)) * step;
+        last = min(first + step - 1, last);
+      }
+      n = first - b;
+    }
+    if (n <= US * NG && grp < n) {
+      d4 v[US][CPL];
+#pragma unroll
+      for (int u = 1; u < US; ++u)
+        if (grp + u * NG < n) slot(2 * int64_t(b + 1 + grp + u * NG), v[u]);
+#pragma unroll
+      for (int u = 1; u < US; ++u) {
+        if (grp + u * NG < n) {
+#pragma unroll
+          for (int j = 0; j < CPL; ++j) sum[j] += v[u][j];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) own[(grp * CPL + j) * LPR + rl] = sum[j];
     }
   }
-  // n: the blocks from b + 1 on whose first look-up is in the segment (kBlock
-  // of them looked at in a round; the keys are sorted, so they come first).
-  int n = 0;
-  for (int base = b + 1;; base += kBlock) {
-    const int c = base + tid;
-    const bool in = c < nblocks && key_of(sorted[uint32_t(c) * span]) == kl;
-    const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-    if (lane == 0) counts[tid / kWave] = __popcll(m);
-    __syncthreads();
-    int k = 0;
+  if (int(threadIdx.x) % kBlock == 0) many[q] = n > US * NG ? n : 0;
+  __syncthreads();
+  if (n > 0 && n <= US * NG && grp == 0) add_and_apply(own, min(n, NG));
+  int lb = 0, ln = 0;  // the boundary with many blocks
 #pragma unroll
-    for (int i = 0; i < kWavesPerBlock; ++i) k += counts[i];
-    __syncthreads();
-    n += k;
-    if (k < kBlock) break;
+  for (int i = 0; i < Q; ++i) {
+    if (many[i] > 0) {
+      lb = int(blockIdx.x) * Q + i;
+      ln = many[i];
+    }
   }
-  if (grp < n) {
+  if (ln == 0) return;  // the same in the whole fix-up block
+  __syncthreads();
+  // What to add: the blocks up to the first full group, the groups' sums, the
+  // blocks after the last of them.
+  const int g0 = (lb + kPre) / kPre * kPre;  // first group from block lb + 1 on
+  const int groups = presummed && lb + ln > g0 ? (lb + ln - g0) / kPre : 0;
+  const int head = groups > 0 ? g0 - (lb + 1) : ln;
+  const int items = ln - groups * (kPre - 1);
+  auto slot_of = [&](int i) {
+    if (i < head) return 2 * int64_t(lb + 1 + i);
+    if (i < head + groups) return 2 * int64_t(g0 + (i - head) * kPre) + 1;
+    return 2 * int64_t(lb + 1 + i + groups * (kPre - 1));
+  };
+  const int g = wave * R + rg;
+  if (g < items) {
     d4 sum[CPL];
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) sum[j] = first[j];
-    constexpr int UF = CPL == 1 ? 4 : 2;
-    for (int c = grp + NG; c < n; c += UF * NG) {
+    for (int j = 0; j < CPL; ++j) sum[j] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int c = g; c < items; c += UF * Q * NG) {
       d4 v[UF][CPL];
 #pragma unroll
       for (int u = 0; u < UF; ++u)
-        if (c + u * NG < n) slot(2 * int64_t(b + 1 + c + u * NG), v[u]);
+        if (c + u * Q * NG < items) slot(slot_of(c + u * Q * NG), v[u]);
 #pragma unroll
       for (int u = 0; u < UF; ++u) {
-        if (c + u * NG < n) {
+        if (c + u * Q * NG < items) {
 #pragma unroll
           for (int j = 0; j < CPL; ++j) sum[j] += v[u][j];
         }
       }
     }
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) part[(grp * CPL + j) * LPR + rl] = sum[j];
+    for (int j = 0; j < CPL; ++j) part[(g * CPL + j) * LPR + rl] = sum[j];
   }
   __syncthreads();
-  if (grp != 0) return;
-  const int m = min(n, NG);
-  for (int k = 0; k < m; ++k) {
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) acc[j] += part[(k * CPL + j) * LPR + rl];
-  }
-#pragma unroll
-  for (int j = 0; j < CPL; ++j) {
-    const int c4 = rl + j * LPR;
-    if (c4 < E4) Rows::store(row, c4, pre[j], acc[j], double(lr));
-  }
+  if (b == lb && grp == 0) add_and_apply(part, min(items, Q * NG));
 }
 
 #define EMB_GEOM(g, MACRO)           \
@@ -539,12 +652,26 @@ void launch_apply(const TableDesc& d, int32_t B, const void* dY, float lr, const
   const uint32_t span = uint32_t(L.chunk) * uint32_t(kBlock / g.lpr);
   const int32_t NS = int32_t(L.ns), C = int32_t(L.chunk);
   const int32_t in_order = apply_in_dispatch_order(blocks, d.num_tables, B, d.dim, GBF16 ? 2 : 4);
+  // A launch more (2 us; 5 where a row of E = 1024 fills a group or two) where the
+  // blocks' partial sums of one row may be over 4 MB, in updates of 80 us and more.
+  // Measured, us per update without / with it, all look-ups of one row and 30% of
+  // them: 500K of E = 256 120 / 52 and 105 / 84, of E = 512 218 / 67 and 194 / 146, of
+  // E = 1024 398 / 119 and 382 / 298; 250K of E = 256 (1954 blocks) 71 / 31 and 60 / 51,
+  // but 51.5 / 53.2 without a hot row, so that the line lies above it.
+  const bool presum = blocks > 1024 && int64_t(blocks) * d.dim > (int64_t(1) << 19);
 #define EMB_SEG(LL, CC)                                                                        \
   hipLaunchKernelGGL((segment_sgd<LL, CC, Rows, MODE, GBF16>), dim3(blocks), dim3(kBlock), 0, st, \
                      d, sorted, NS, C, dY, B, inv_b, lr, carry, flags, token, pd, in_order);   \
+  if (presum)                                                                                  \
+    hipLaunchKernelGGL((segment_presum<LL, CC>),                                               \
+                       dim3((blocks / kPre + kBlock / LL - 1) / (kBlock / LL)), dim3(kBlock), 0, \
+                       st, sorted, span, blocks, d.dim, carry, flags, token);                  \
   if (blocks > 1)                                                                              \
-  hipLaunchKernelGGL((segment_fixup<LL, CC, Rows>), dim3(blocks - 1), dim3(kBlock), 0, st, d,   \
-                     sorted, NS, span, blocks, B, inv_b, lr, carry, flags, token)
+    hipLaunchKernelGGL((segment_fixup<LL, CC, Rows>),                                            \
+                     dim3((blocks - 1 + kFixThreads<LL, CC> / kBlock - 1) /                    \
+                          (kFixThreads<LL, CC> / kBlock)),                                     \
+                     dim3(kFixThreads<LL, CC>), 0, st, d, sorted, NS, span, blocks, B, inv_b,   \
+                     lr, carry, flags, token, presum)
   EMB_GEOM(g, EMB_SEG)
 #undef EMB_SEG
 }

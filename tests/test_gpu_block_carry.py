@@ -52,16 +52,34 @@ def test_segments_around_chunks_and_blocks(dim, split):
     _check(lengths, dim, split, rng, f"blocks of {span} E={dim}")
 
 
-@pytest.mark.parametrize("dim,extra", [(64, 0), (256, 1), (1024, -1)])
-def test_segment_over_many_blocks(dim, extra):
-    """A segment over more blocks than a fix-up block looks at in one round (256),
-    and one over more than it has row groups; both end at, before or after a
-    block's edge."""
+@pytest.mark.parametrize("dim,split,extra", [(4, False, 0), (8, True, 1), (16, False, -1), (64, False, 0),
+                                             (128, True, -1), (256, False, 1), (512, True, 0),
+                                             (768, False, 1), (1024, False, -1)])
+def test_segment_over_many_blocks(dim, split, extra):
+    """A segment over more blocks than the fix-up looks at in one step (64, then a
+    search), and segments over about as many as a boundary's own row groups add (4,
+    2 or 1 each); all end at, before or after a block's edge."""
     lanes = _lanes(dim)
     groups = 256 // lanes
     span = (32 if lanes == 64 else 8) * groups
-    _check(np.array([span - 3, 258 * span + 3 + extra, 5, (groups + 2) * span + 1]), dim, False,
+    own = groups * {1: 4, 2: 2}.get(-(-dim // 256), 1)
+    _check(np.array([span - 3, 258 * span + 3 + extra, 5, (groups + 2) * span + 1, own * span - 1,
+                     own * span, own * span + 1, (own + 1) * span + 2]), dim, split,
            np.random.default_rng(dim), f"long segment E={dim}")
+
+
+@pytest.mark.parametrize("dim,blocks,lead", [(128, 4098, 0), (128, 4098, 15)] + [
+    (dim, blocks, lead) for dim, blocks in ((256, 2050), (512, 1026), (1024, 1040))
+    for lead in (0, 1, 14, 15, 16, 33)])
+def test_groups_of_blocks_are_presummed(dim, blocks, lead):
+    """Calls whose partial sums may be over 4 MB: one segment fills groups of 16
+    blocks, beginning and ending at every kind of place in its first and last group."""
+    span = 256 * 8 if dim == 128 else 128
+    lengths = [lead * span + 7] if lead else []
+    tail = {0: 40, 1: 16 * 3 + 1, 14: 31, 15: 32, 16: 20, 33: 100}[lead]
+    rest = blocks * span - sum(lengths) - tail * span
+    _check(np.array(lengths + [tail * span - 5, rest // 3, rest - rest // 3 - 3, 1]), dim, dim == 512,
+           np.random.default_rng(lead), f"presummed groups E={dim} lead={lead}")
 
 
 @pytest.mark.parametrize("ns", [1, 7, 8, 9, 127, 128, 129, 255, 256, 257])
