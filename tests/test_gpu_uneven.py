@@ -85,3 +85,10 @@ def test_update_of_one_row(dim, limit):
     even, one = (Call([100_000], 12_500, [40], dim, hot).us("apply") for hot in (0.0, 1.0))
     log(f"[uneven] update E={dim} 500K look-ups: many rows {even:.1f} us, one row {one:.1f} us")
     assert one <= limit * even
+
+
+# (read one by one, the sums of 256 row groups: 2.5 times the wider rows')
+def test_update_of_narrow_rows():
+    narrow, wide = (Call([100_000], 1250, [40], dim, 1.0).us("apply") for dim in (4, 32))
+    log(f"[uneven] update of one row, 50K look-ups: E=4 {narrow:.1f} us, E=32 {wide:.1f} us")
+    assert narrow <= 1.9 * wide
