@@ -143,30 +143,41 @@ __device__ __forceinline__ bool fill_bags(const int32_t* O, int lo, int hi, int 
   }
   __syncthreads();
   // As many threads per bag as the bags leave, so that a long bag is not one
-  // thread's loop.
+  // thread's loop; where few of many bags are in the tile (a table of long bags)
+  // that is one each, and a wavefront then fills its lanes' long ones together.
   const int k0 = known ? lo : krange[0];
   const int nb = max((known ? hi : krange[1]) - k0 + 1, 0);
   int share = 1;
   while (share < kThreads && int64_t(share) * 2 * nb <= kThreads) share *= 2;
   const int lead = tid % share, stride = kThreads / share;
-  for (int64_t q0 = tid / share; q0 < nb; q0 += int64_t(stride) * Q) {
+  for (int64_t q0 = 0; q0 < nb; q0 += int64_t(stride) * Q) {  // uniform over the block
     int oa[Q], ob[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const int64_t k = q0 + q * stride;
+      const int64_t k = q0 + tid / share + q * stride;
       oa[q] = k < nb ? O[k0 + k] : 0;
       ob[q] = k < nb ? O[k0 + k + 1] : 0;
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const int64_t k = q0 + q * stride;
-      if (k >= nb) break;
-      if constexpr (CHECK) bad = bad || bad_offset(k, oa[q], ob[q], NS, TB);
+      if (q0 + q * stride >= nb) break;  // uniform over the block
+      const int64_t k = q0 + tid / share + q * stride;
+      if constexpr (CHECK) bad = bad || (k < nb && bad_offset(k, oa[q], ob[q], NS, TB));
       // (both ends forced into the tile before they are moved: a bad offset may
-      // be any int)
+      // be any int; past the last bag both are 0 and give an empty range)
       const int a = min(max(oa[q], start), start + count) - start;
       const int b = min(max(ob[q], start), start + count) - start;
-      for (int s = a + lead; s < b; s += share) lbag[s] = uint32_t(k0 + k);
+      const uint32_t bag = uint32_t(k0 + k);
+      const bool lengthy = share <= 4 && b - a > 128 * share;
+      if (!lengthy)
+        for (int s = a + lead; s < b; s += share) lbag[s] = bag;
+      if (share > 4) continue;
+      for (uint64_t m = __builtin_amdgcn_ballot_w64(lengthy && lead == 0); m != 0; m &= m - 1) {
+        const int l = int(__builtin_ctzll(m));
+        const int from = __builtin_amdgcn_readlane(a, l), to = __builtin_amdgcn_readlane(b, l);
+        const uint32_t of = uint32_t(__builtin_amdgcn_readlane(int(bag), l));
+        for (int s = from + lane; s < to; s += kWave) lbag[s] = of;
+      }
     }
   }
   __syncthreads();

@@ -67,8 +67,29 @@ CASES = {
     "by table, 64 tables": ((50000,) * 64, 40, (1,) * 31 + (0,) + (3300,) * 32),
     "by table, last per table": ((300000,), 900, (262144,)),
     "whole list, first per table": ((300000,), 900, (262145,)),
+    "few long bags of many": ((30000, 9, 1 << 20), 700, (2100, 699, 200000)),
+    "long bags, one block": ((300, 70), 300, (3000, 600)),
     "by table, most skewed": ((300000, 5, 5, 5, 5, 5, 5), 900, (1835008, 0, 0, 0, 0, 0, 0)),
 }
+
+
+def test_bags_of_any_length_in_a_tile():
+    """Bags of 1 to 5000 look-ups, long ones filled by a wavefront together (more
+    than 128 per thread of the bag), among as many empty ones as leave a bag one, two
+    or four threads."""
+    rng = np.random.default_rng(11)
+    for bags, longest in ((300, 600), (600, 130), (600, 1500), (1100, 5000), (5000, 900)):
+        sizes = np.where(rng.random(bags) < 0.03, rng.integers(100, longest + 1, bags),
+                         rng.integers(0, 2, bags))
+        for d in (127, 128, 129, 256, 257, 512, 513):
+            sizes[rng.integers(0, bags)] = min(d, longest)
+        print(bags, longest, int(sizes.sum()), flush=True)
+        O = np.r_[0, np.cumsum(np.r_[sizes, sizes[::-1]])].astype(np.int32)
+        I = rng.integers(0, 40000, O[-1]).astype(np.int32)
+        rc, status, got = gpu_dedup((40000, 50000), bags, I, O)
+        key, bag, uniq, seg = _reference((40000, 50000), bags, I, O)
+        assert rc == 0 and status == 0
+        assert np.array_equal(got["sorted_keys"], key) and np.array_equal(got["sorted_bags"], bag)
 
 
 @pytest.mark.parametrize("name", CASES)

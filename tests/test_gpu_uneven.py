@@ -39,15 +39,20 @@ def graph_us(fn, n=10, rounds=7):
 
 class Call:
     """One call's buffers: `bags` look-ups per bag of each table, uniform over its rows, a share
-    `hot` of them of row 0."""
+    `hot` of them of row 0; with `cut` the bags are cut at random (a few of them long)."""
 
-    def __init__(self, rows, batch, bags, dim, hot=0.0):
+    def __init__(self, rows, batch, bags, dim, hot=0.0, cut=False):
         T = len(rows)
         g = torch.Generator(device=DEV)
         g.manual_seed(1)
         sizes = torch.tensor(bags, device=DEV).repeat_interleave(batch)
         offsets = torch.zeros(T * batch + 1, dtype=torch.int64, device=DEV)
         torch.cumsum(sizes, 0, out=offsets[1:])
+        if cut:
+            for t, p in enumerate(bags):
+                o = offsets[t * batch:(t + 1) * batch + 1]
+                at = torch.rand(batch - 1, device=DEV, generator=g).sort()[0]
+                o[1:-1] = o[0] + (at * (batch * p)).long()
         idx = []
         for m, p in zip(rows, bags):
             r = torch.randint(0, m, (batch * p,), dtype=torch.int32, device=DEV, generator=g)
@@ -92,3 +97,13 @@ def test_update_of_narrow_rows():
     narrow, wide = (Call([100_000], 1250, [40], dim, 1.0).us("apply") for dim in (4, 32))
     log(f"[uneven] update of one row, 50K look-ups: E=4 {narrow:.1f} us, E=32 {wide:.1f} us")
     assert narrow <= 1.9 * wide
+
+
+def test_prepare_with_few_long_bags():
+    """One table of 641 bags of 296 look-ups on average, some of them 1500, among tables of one
+    look-up per bag: the bags of a tile are few of its table's, and long (3.0 times the even call
+    when each was one thread's loop)."""
+    long, even = (Call([1_000_000] * 26, 641, bags, 16, cut=True).us("prepare")
+                  for bags in ([296] + [1] * 25, [12] * 26))
+    log(f"[uneven] prepare of 200K look-ups over 26 tables: long bags {long:.1f} us, even {even:.1f} us")
+    assert long <= 2.1 * even
