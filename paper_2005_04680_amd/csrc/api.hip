@@ -173,12 +173,13 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   // Radix passes inside each table: two for tables of up to 2^20 rows instead
   // of three, in four launches instead of nine.  A block of the scatter adds up
   // the counts of its table's tiles by itself, so that the work grows with the
-  // square of the tiles per table.  Measured, us per prepare, whole list / by
-  // table: 120K look-ups over 2 tables 33.9 / 25.2; 300K over 40 42.2 / 27.5;
-  // 524K over 8 (16 tiles of 4096 each) 43.9 / 30.7; 819K over 8 54.4 / 36.8;
-  // 525K weighted over 5 of 3M rows 52.2 / 42.9; 1.7M over 26 73.9 / 63.7; 2M
-  // over 8 69.2 / 63.6; 400K in one table (98 tiles) 45.5 / 48.7; 1M in one (244)
-  // 44.6 / 61.4; 13.1M over 16 (200 each) 253 / 275.
+  // square of the tiles per table, of which one may have nearly all.  Measured, us
+  // per prepare, whole list / by table: evenly 120K look-ups over 2 tables 33.3 /
+  // 24.8; 328K over 40 41.7 / 23.3; 524K over 8 44.4 / 30.9; 819K over 8 57.8 / 36.6;
+  // 525K weighted over 5 of 3M rows 52.2 / 42.9; 1.7M over 26 78.7 / 47.9; 246K in
+  // one table 33.0 / 29.2; one long table of 8 or 26: 401K 36.6 / 34.1, 1.04M 50.9 /
+  // 48.8, 1.72M 56.5 / 52.7, 2M 59.4 / 59.2.  (The limit per table is from sums of two
+  // counts a word: 400K in one table 45.5 / 48.7.)
   L.by_table = !L.small && NS > 0 && NS <= kTableSort && NS <= int64_t(T) * kTableSortPerTable &&
                int64_t(T) * B <= 2 * NS;
   L.sorted_in_b = !L.small && !L.by_table && NS > 0 && L.passes % 2 == 1;

@@ -25,8 +25,8 @@ constexpr int kMaxItemsPerThread = 16;  // radix tile: kBlock * (4, 8 or 16) key
 constexpr int kReduceBlocks = kNumCu * 4;  // blocks of the segmented reduce that run at once
 constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block validates, at most
 
-// Which calls are sorted table by table, in tiles of 4096 look-ups (see
-// backward_layout).
+// Which calls are sorted tile by tile or table by table, in units of 4096 look-ups
+// (see backward_layout).
 constexpr int kSmallSort = 24 * 4096;
 constexpr int kSmallPerTable = 8 * 4096;
 constexpr int kSmallOffsets = 32768;

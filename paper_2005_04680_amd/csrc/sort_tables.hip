@@ -2,22 +2,32 @@
 //
 // The look-ups of a table are one contiguous range already, so a radix pass
 // inside each table needs no digit of the table: digits of up to 10 bits cover
-// tables of 2^20 rows in two passes.  A tile (4096 look-ups of one table) is a
-// block of 16 wavefronts with a digit per thread.  No kernel scans the tiles'
-// counts: a table has few tiles, and each block of the scatter adds up those
-// of its own (16 of them are 32 KB of 16-bit counts, read from the L2 in one
-// round) while it ranks its keys.
+// tables of 2^20 rows in two passes.  A tile (2048, 4096 or 8192 look-ups of one
+// table) is a block of 16 wavefronts with a digit per thread.  No kernel scans the
+// tiles' counts: each block of the scatter adds up those of its own table by itself
+// (16 tiles are 32 KB of 16-bit counts, read from the L2 in one round) while it
+// ranks its keys.
 //
-// Bound by latency: at 524K look-ups over 8 tables (132 blocks) the keys take
-// 7 us, a scatter 10 (the counts' sums, the ranks, four barriers, the store of
+// Bound by latency: at 524K look-ups over 8 tables (264 blocks) the keys take
+// 5 us, a scatter 7 to 10 (the counts' sums, the ranks, four barriers, the store of
 // runs of 4 keys), the second pass's counts 4; three passes of 8 bits over the
 // whole list took 6 + 3 * (4 + 7) + 2 * 3 in nine launches.
+//
+// The counts of a table that holds nearly all look-ups are read by as many blocks
+// as it has tiles, n^2 * 2 KB of reads from the L2s a pass.  Words of eight counts
+// per lane and larger tiles for more look-ups keep that below what the whole
+// list's passes take; us per prepare, whole list / words of two counts and tiles
+// of at most 4096 / now, one long table among 8 (of 1M rows, the others of 100):
+// 520K 39.5 / 52.3 / 39.2, 1.04M 50.9 / 61.1 / 48.8, 2M 59.4 / 132 / 59; with all tables
+// of 1M rows 46.8 / 52.6 / 39.0, 65.5 / 61.5 / 48.6, 76.7 / 132 / 58.
 //
 // The result is that of the whole list's radix sort, bit for bit.
 #include "sort_tile.hpp"
 
 namespace embbag {
 namespace {
+
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 // Keys of one tile and its counts of the first digit; `vb` of the offsets.
 template <int ITEMS>
@@ -107,11 +117,15 @@ __global__ __launch_bounds__(kThreads) void table_counts(
 }
 
 // Stable scatter of a tile by the digit at `shift` inside its table.  A block
-// sums the counts of its table's tiles by itself: R 16-bit counts a tile, two
-// to a word, the block's threads taking as many tiles at a time as they span.
-// FIRST: one more block folds the status words.
-template <int ITEMS, bool VALS, bool FIRST>
-__global__ __launch_bounds__(kThreads, ITEMS == 4 ? 8 : 4) void table_scatter(
+// sums the counts of its table's tiles by itself: R 16-bit counts a tile, eight
+// per thread, the block's threads taking as many tiles at a time as they span and
+// as give each four.  FIRST: one more block folds the status words.  TWO: held to
+// 64 registers, so that two blocks share a compute unit, where the blocks are more
+// than those (1.7M look-ups in tiles of 4096 64 us instead of 70, 700K in 171
+// blocks 36.8 instead of 36.1).  With values in tiles of 4096 the LDS has room for
+// one block only.
+template <int ITEMS, bool VALS, bool FIRST, bool TWO>
+__global__ __launch_bounds__(kThreads, TWO ? 8 : 4) void table_scatter(
     TableDesc d, const uint64_t* __restrict__ src, uint64_t* __restrict__ dst,
     const Tile* __restrict__ info, int32_t shift, int32_t bits,
     const uint16_t* __restrict__ hist, const float* __restrict__ vsrc, float* __restrict__ vdst,
@@ -150,6 +164,8 @@ __global__ __launch_bounds__(kThreads, ITEMS == 4 ? 8 : 4) void table_scatter(
     item[i] = valid[i] ? src[me.start + j] : 0ull;
     if constexpr (VALS) val[i] = valid[i] ? vsrc[me.start + j] : 0.f;
   }
+  for (int i = tid; i < (kWaves << bits) / 2; i += kThreads)
+    reinterpret_cast<uint32_t*>(whist)[i] = 0;
   // Counts of the table's tiles: all (tot) and before this one (pre).
   tot[tid] = 0;
   pre[tid] = 0;
@@ -157,30 +173,37 @@ __global__ __launch_bounds__(kThreads, ITEMS == 4 ? 8 : 4) void table_scatter(
     reinterpret_cast<uint32_t*>(whist)[i] = 0;
   __syncthreads();
   {
-    const int words = R / 2, col = tid & (words - 1), lead = tid / words;
-    const int stride = kThreads / words;  // words <= 512
-    const uint32_t* h = reinterpret_cast<const uint32_t*>(hist) + size_t(me.first) * words + col;
+    constexpr int Q = 4;  // rows requested together
+    const int words = R / 8, col = tid & (words - 1), lead = tid / words;
+    const int leads = min(kThreads / words, (me.tiles + Q - 1) / Q);  // words <= 128
+    const u4* h = reinterpret_cast<const u4*>(hist) + size_t(me.first) * words + col;
     const int mine = blk - me.first;
-    uint32_t t0 = 0, t1 = 0, p0 = 0, p1 = 0;
-    constexpr int Q = 8;
-    for (int r0 = lead; r0 < me.tiles; r0 += stride * Q) {
-      uint32_t c[Q];
+    if (lead < leads) {
+      u4 all_lo{}, all_hi{}, pre_lo{}, pre_hi{};  // of digits 8 col + 0, 2, 4, 6 and 1, 3, 5, 7
+      for (int r0 = lead; r0 < me.tiles; r0 += leads * Q) {
+        u4 c[Q];
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
-        c[q] = r0 + q * stride < me.tiles ? h[size_t(r0 + q * stride) * words] : 0u;
+        for (int q = 0; q < Q; ++q)
+          c[q] = r0 + q * leads < me.tiles ? h[size_t(r0 + q * leads) * words] : u4{};
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const bool before = r0 + q * stride < mine;
-        t0 += c[q] & 0xFFFFu;
-        t1 += c[q] >> 16;
-        p0 += before ? c[q] & 0xFFFFu : 0u;
-        p1 += before ? c[q] >> 16 : 0u;
+        for (int q = 0; q < Q; ++q) {
+          const u4 lo = c[q] & 0xFFFFu, hi = c[q] >> 16;
+          all_lo += lo;
+          all_hi += hi;
+          if (r0 + q * leads < mine) {
+            pre_lo += lo;
+            pre_hi += hi;
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (all_lo[i]) atomicAdd(&tot[8 * col + 2 * i], all_lo[i]);
+        if (all_hi[i]) atomicAdd(&tot[8 * col + 2 * i + 1], all_hi[i]);
+        if (pre_lo[i]) atomicAdd(&pre[8 * col + 2 * i], pre_lo[i]);
+        if (pre_hi[i]) atomicAdd(&pre[8 * col + 2 * i + 1], pre_hi[i]);
       }
     }
-    if (t0) atomicAdd(&tot[2 * col], t0);
-    if (t1) atomicAdd(&tot[2 * col + 1], t1);
-    if (p0) atomicAdd(&pre[2 * col], p0);
-    if (p1) atomicAdd(&pre[2 * col + 1], p1);
   }
   const uint32_t base = d.rowbase[me.table];
   uint32_t dig[ITEMS], rank[ITEMS];
@@ -190,7 +213,7 @@ __global__ __launch_bounds__(kThreads, ITEMS == 4 ? 8 : 4) void table_scatter(
   __syncthreads();
   const uint32_t mine_tot = tid < R ? tot[tid] : 0u;
   const uint32_t to = scan_block(mine_tot, scratch[0]) + (tid < R ? pre[tid] : 0u);
-  const uint32_t first = place_digits<ITEMS == 2>(bits, whist, scratch[1]);
+  const uint32_t first = place_digits<!TWO>(bits, whist, scratch[1]);
   __syncthreads();
   // (tot is free: it now holds a digit's place in the table less that in the tile)
   if (tid < R) tot[tid] = to - first;
@@ -235,6 +258,7 @@ hipError_t sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const in
   uint64_t* dst = reinterpret_cast<uint64_t*>(ws + (passes % 2 ? L.off_a : L.off_b));
   float* vdst = reinterpret_cast<float*>(ws + (passes % 2 ? L.off_va : L.off_vb));
   float* vother = reinterpret_cast<float*>(ws + (passes % 2 ? L.off_vb : L.off_va));
+  const bool two = blocks > kNumCu;
   const float* vsrc = A;  // the first pass reads the caller's weights
   hipLaunchKernelGGL(table_keys<ITEMS>, dim3(blocks), dim3(kThreads), 0, st, d, I, O, ns, B, TB, vb, bits,
                      src, hist, info, status);
@@ -244,7 +268,7 @@ hipError_t sort_tables(const TableDesc& d, int32_t B, const int32_t* I, const in
       hipLaunchKernelGGL(table_counts<ITEMS>, dim3(blocks), dim3(kThreads), 0, st, d, src, info, shift,
                          bits, hist);
 #define EMB_SCATTER(VALS, FIRST)                                                                 \
-  hipLaunchKernelGGL((table_scatter<ITEMS, VALS, FIRST>), dim3(blocks + (FIRST ? 1 : 0)),               \
+  hipLaunchKernelGGL((two ? table_scatter<ITEMS, VALS, FIRST, ITEMS == 4 && !VALS> : table_scatter<ITEMS, VALS, FIRST, false>), dim3(blocks + (FIRST ? 1 : 0)),               \
                      dim3(kThreads), 0, st, d, src, dst, info, shift, bits, hist, vsrc, vdst,    \
                      status, blocks, flags, d_status, token)
     if (A != nullptr && p == 0) EMB_SCATTER(true, true);
@@ -270,18 +294,25 @@ hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, c
   uint32_t rows = 2;  // of the largest table: its bits decide the digits
   for (int t = 0; t < d.num_tables; ++t) rows = d.rows[t] > rows ? d.rows[t] : rows;
   const int nbits = 32 - __builtin_clz(rows - 1u);
-  const int passes = (nbits + kMaxDigitBits - 1) / kMaxDigitBits;
-  const int bits = (nbits + passes - 1) / passes;
-  // Tiles of 2048 look-ups while they are at most a block per compute unit
-  // (524K 31 us instead of 33, 213K over 26 tables 27 instead of 32, 819K 47
-  // instead of 36) and their counts fit the workspace; tiles of 4096 then run
-  // two blocks to a compute unit (64 registers; 1.7M look-ups 64 us, 70 with
-  // one).
+  const int fewest = (nbits + kMaxDigitBits - 1) / kMaxDigitBits;
+  auto digits = [&](int passes) { return (nbits + passes - 1) / passes > 3 ? (nbits + passes - 1) / passes : 3; };
   const size_t room = L.off_tot - L.off_hist;
-  if (NS <= int64_t(kNumCu) * 2 * kThreads && scratch_bytes(NS, d.num_tables, 2, bits) <= room)
-    return sort_tables<2>(d, B, I, O, NS, L, ws, d_status, token, A, passes, bits, st);
-  if (scratch_bytes(NS, d.num_tables, 4, bits) > room) return hipErrorInvalidValue;
-  return sort_tables<4>(d, B, I, O, NS, L, ws, d_status, token, A, passes, bits, st);
+  auto fits = [&](int items, int passes) {
+    return scratch_bytes(NS, d.num_tables, items, digits(passes)) <= room;
+  };
+  // Tiles of 2048 look-ups while they are at most a block per compute unit (524K
+  // over 8 tables 31 us instead of 33, 213K over 26 22 instead of 27) and their
+  // counts fit the workspace, of 8192 beyond a block of 4096 per compute unit
+  // while they are at most one again, with a table's last half full on average
+  // (1.7M look-ups over 26 tables, then over 8: 48 and 50 us instead of 54 and 62;
+  // 260 blocks instead of 512 in two halves 78 instead of 58).
+  if (NS <= int64_t(kNumCu) * 2 * kThreads && fits(2, fewest))
+    return sort_tables<2>(d, B, I, O, NS, L, ws, d_status, token, A, fewest, digits(fewest), st);
+  if (NS > int64_t(kNumCu) * 4 * kThreads &&
+      NS + int64_t(d.num_tables) * 4 * kThreads <= int64_t(kNumCu) * 8 * kThreads && fits(8, fewest))
+    return sort_tables<8>(d, B, I, O, NS, L, ws, d_status, token, A, fewest, digits(fewest), st);
+  if (!fits(4, fewest)) return hipErrorInvalidValue;
+  return sort_tables<4>(d, B, I, O, NS, L, ws, d_status, token, A, fewest, digits(fewest), st);
 }
 
 }  // namespace embbag

@@ -69,6 +69,12 @@ CASES = {
     "whole list, first per table": ((300000,), 900, (262145,)),
     "few long bags of many": ((30000, 9, 1 << 20), 700, (2100, 699, 200000)),
     "long bags, one block": ((300, 70), 300, (3000, 600)),
+    "by table, 32 tiles of a table and 33": ((1 << 20, 1 << 19), 3000, (65536, 65537)),
+    "by table, first of 8192": ((1 << 20, 70000, 9, 5), 9000, (1040384, 8192, 1, 0)),
+    "by table, 8192 and remainders": ((1 << 20,) * 6, 9000, (8191, 8193, 16384, 900000, 300001, 77)),
+    "by table, last of 8192": ((1 << 20, 3, 3, 3, 3, 3, 3, 3), 9000, (2064384, 0, 0, 0, 0, 0, 0, 0)),
+    "by table, first past 8192": ((1 << 20, 3, 3, 3, 3, 3, 3, 3), 9000, (2064385, 0, 0, 0, 0, 0, 0, 0)),
+    "by table, digits of 3 bits": ((2, 5, 2), 900, (70000, 40000, 3)),
     "by table, most skewed": ((300000, 5, 5, 5, 5, 5, 5), 900, (1835008, 0, 0, 0, 0, 0, 0)),
 }
 
@@ -139,7 +145,7 @@ def test_data_errors(counts):
 
 
 @pytest.mark.parametrize("counts", [(2000, 1500), (9000, 4097), (30000, 4097), (50000, 70000),
-                                    (300000, 230000)])
+                                    (300000, 230000), (490000, 33000)])
 def test_weights_travel_with_the_look_ups(counts):
     rows, batch, dim = (900, 40000), 77, 12
     rng = np.random.default_rng(5)

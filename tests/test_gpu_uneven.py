@@ -107,3 +107,16 @@ def test_prepare_with_few_long_bags():
                   for bags in ([296] + [1] * 25, [12] * 26))
     log(f"[uneven] prepare of 200K look-ups over 26 tables: long bags {long:.1f} us, even {even:.1f} us")
     assert long <= 2.1 * even
+
+
+# (2.0, 1.64 and 2.35 times the even call where the counts were read in words of two,
+# by tiles of at most 4096; 1.46, 1.29 and 1.26 now: the limits lie between)
+@pytest.mark.parametrize("batch,long,each,limit", [(4096, 120, 16, 1.72), (8192, 120, 16, 1.46),
+                                                   (16384, 115, 15, 1.75)])
+def test_prepare_of_one_long_table(batch, long, each, limit):
+    """Most look-ups in one of 8 tables, against the same number shared by all: a block of the
+    scatter reads the counts of its table's tiles."""
+    one, even = (Call([1_000_000] + [100] * 7, batch, bags, 16).us("prepare")
+                 for bags in ([long] + [1] * 7, [each] * 8))
+    log(f"[uneven] prepare of {batch * (long + 7)} look-ups over 8 tables: one long {one:.1f} us, even {even:.1f} us")
+    assert one <= limit * even
