@@ -161,13 +161,15 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   L.bits = L.passes > 0 ? (nbits + L.passes - 1) / L.passes : 6;
   if (L.bits < 6) L.bits = 6;
   // Tile by tile in LDS while that takes fewer and shorter kernels than the
-  // radix sort's nine (31 to 36 us whatever the size): up to 24 tiles and, the
-  // merge searching every tile of a table, 8 per table if the tables share the
-  // look-ups evenly.  Measured, us per prepare, radix / tiles: 512 look-ups 18.5
-  // / 6.6; 13K over 26 tables 34.0 / 12.1; 59K over 8 33.8 / 19.7; 81K over 3
-  // (7 tiles each) 31.0 / 23.7; 120K over 2 (15 each) 33.9 / 31.8; 102K in one
-  // table (25) 31.3 / 42.7.  With many more bags than look-ups the offsets are
-  // the work, and the radix sort's key build spreads them over more blocks.
+  // radix sort's nine (31 to 36 us whatever the size).  The merge searches every
+  // tile of a table, and one table may hold nearly all look-ups: up to 15 tiles of
+  // 4096 in all, 8 per table on average.  Measured, us per prepare, radix / tiles,
+  // tables that share the look-ups evenly: 512 look-ups 18.5 / 6.6; 13K over 26
+  // tables 34.0 / 12.1; 59K over 8 33.8 / 16.3; 53K over 26 31.0 / 12.1; one long
+  // table: 35K of 8 33.0 / 28.9, 54K of 26 31.9 / 29.2, 54K of 8 32.1 / 34.0, but 96K
+  // of 8 34.7 / 48.8 (and 26.7 by table, where 90K over 8 take 21.0 evenly, 17.6 by
+  // tiles).  With many more bags than look-ups the offsets are the work, and the
+  // radix sort's key build spreads them over more blocks.
   L.small = NS > 0 && NS <= kSmallSort && NS <= int64_t(T) * kSmallPerTable &&
             int64_t(T) * B <= (2 * NS > kSmallOffsets ? 2 * NS : kSmallOffsets);
   // Radix passes inside each table: two for tables of up to 2^20 rows instead

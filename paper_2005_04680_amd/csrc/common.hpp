@@ -27,7 +27,7 @@ constexpr int64_t kOffsetsPerBlock = 16384;  // offsets a key-build block valida
 
 // Which calls are sorted tile by tile or table by table, in units of 4096 look-ups
 // (see backward_layout).
-constexpr int kSmallSort = 24 * 4096;
+constexpr int kSmallSort = 15 * 4096;
 constexpr int kSmallPerTable = 8 * 4096;
 constexpr int kSmallOffsets = 32768;
 constexpr int64_t kTableSort = 512 * 4096;

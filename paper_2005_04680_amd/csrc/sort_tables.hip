@@ -311,8 +311,12 @@ hipError_t launch_sort_tables(const TableDesc& d, int32_t B, const int32_t* I, c
   if (NS > int64_t(kNumCu) * 4 * kThreads &&
       NS + int64_t(d.num_tables) * 4 * kThreads <= int64_t(kNumCu) * 8 * kThreads && fits(8, fewest))
     return sort_tables<8>(d, B, I, O, NS, L, ws, d_status, token, A, fewest, digits(fewest), st);
-  if (!fits(4, fewest)) return hipErrorInvalidValue;
-  return sort_tables<4>(d, B, I, O, NS, L, ws, d_status, token, A, fewest, digits(fewest), st);
+  // A pass more where 10-bit counts do not fit: few look-ups over many tables of
+  // which only one is long (62K over 64).
+  int passes = fewest;
+  while (passes < 4 && !fits(4, passes)) ++passes;
+  if (!fits(4, passes)) return hipErrorInvalidValue;
+  return sort_tables<4>(d, B, I, O, NS, L, ws, d_status, token, A, passes, digits(passes), st);
 }
 
 }  // namespace embbag

@@ -75,6 +75,11 @@ CASES = {
     "by table, last of 8192": ((1 << 20, 3, 3, 3, 3, 3, 3, 3), 9000, (2064384, 0, 0, 0, 0, 0, 0, 0)),
     "by table, first past 8192": ((1 << 20, 3, 3, 3, 3, 3, 3, 3), 9000, (2064385, 0, 0, 0, 0, 0, 0, 0)),
     "by table, digits of 3 bits": ((2, 5, 2), 900, (70000, 40000, 3)),
+    "tiles, last size": ((200000,) * 4, 3000, (30000, 30000, 1000, 440)),
+    "tiles, first size past it": ((200000,) * 4, 3000, (30000, 30000, 1000, 441)),
+    "tiles, all in one table": ((300000, 10, 10), 500, (61440, 0, 0)),
+    "by table, counts of a narrower digit": ((1000000,) + (100,) * 63, 40, (970,) * 64),
+    "by table, the same of 4096 in one": ((1000000,) + (100,) * 63, 40, (62000,) + (7,) * 63),
     "by table, most skewed": ((300000, 5, 5, 5, 5, 5, 5), 900, (1835008, 0, 0, 0, 0, 0, 0)),
 }
 
