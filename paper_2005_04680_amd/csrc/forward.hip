@@ -365,6 +365,19 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
   const int least = avg <= 1 ? 4 : 1;
   const int64_t fill = avg <= 1 ? 1024 : 2048;
   while (G > least && TB < fill * per_block * G) G /= 2;
+  // The order below is chosen for these groups: where one table holds most of
+  // the work, one range of blocks per XCD would leave it to one XCD.
+  const int64_t order_blocks = (int64_t(d.num_tables) * ((B + G - 1) / G) + per_block - 1) / per_block;
+  // The average says nothing of a table of long lists among tables of short ones,
+  // and its groups are each one row group's chain of loads: where a table's groups
+  // are fewer than two blocks per compute unit they are of 8 look-ups' worth, two
+  // bags at least (26 tables of 16384 bags of E = 64, 80 look-ups in one table's and
+  // one in the others': 4 bags 78 us, two 48; four look-ups in all 50.1, 50.6; 213K
+  // bags of 3, E = 64: 5 bags 23.7, two 22.7, of E = 256 102.1, 105.8).
+  if (avg > 1 && d.num_tables > 1) {
+    const int few = avg < 4 ? int(8 / avg) : 2;
+    if (G > few && B < int64_t(2 * kNumCu) * per_block * G) G = few;
+  }
   const int gpt = (B + G - 1) / G;
   const int64_t items = int64_t(d.num_tables) * gpt;
   // Blocks of one wavefront where four would leave compute units idle (128
@@ -376,7 +389,7 @@ hipError_t launch_forward(const TableDesc& d, bool split, int32_t B, const int32
   const int32_t ns = int32_t(NS), it = int32_t(items);
   // A table's touched rows are at most its look-ups' rows.
   const int64_t row_bytes = int64_t(d.dim) * (split ? 2 : 4);
-  const int32_t in_order = dispatch_order(grid.x, d.num_tables, NS / d.num_tables * row_bytes);
+  const int32_t in_order = dispatch_order(order_blocks, d.num_tables, NS / d.num_tables * row_bytes);
   bool ok = false;
   if (split && y_bf16)
     ok = dispatch<true, kPoolPlain, true>(g, grid, st, d, I, O, ns, B, G, gpt, it, Y, status,

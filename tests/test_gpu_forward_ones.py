@@ -63,6 +63,28 @@ def test_pooled_bits(dim, batch, kind):
     assert gs.read_status() == 0
 
 
+@pytest.mark.parametrize("dim,T,batch,avg", [(256, 26, 1300, 2), (256, 26, 1300, 3), (256, 26, 1301, 4),
+                                             (256, 33, 1299, 7), (64, 12, 11003, 4), (20, 40, 8000, 3)])
+@pytest.mark.parametrize("kind", ["even", "ragged", "one long table"])
+def test_pooled_bits_of_short_groups(dim, T, batch, avg, kind):
+    """Grids large enough for groups of several bags whose tables have few groups."""
+    rng = np.random.default_rng(dim + avg)
+    sizes = np.full((T, batch), avg)
+    if kind == "ragged":
+        sizes = rng.integers(0, 2 * avg + 1, (T, batch))
+    elif kind == "one long table":
+        sizes[:] = 1
+        sizes[T // 2] = T * (avg - 1) + rng.integers(0, 3, batch)
+    O = np.r_[0, np.cumsum(sizes.ravel())].astype(np.int32)
+    I = rng.integers(0, 900, O[-1]).astype(np.int32)
+    W = [rng.standard_normal((900, dim)).astype(np.float32) for _ in range(T)]
+    print(dim, T, batch, avg, kind, I.size, flush=True)
+    gt = GpuTables(W)
+    rc, Y = gt.forward(batch, I, O)
+    assert rc == 0 and gt.read_status() == 0
+    assert bits_equal(Y.cpu().numpy(), oracle.forward(W, batch, I, O)[1])
+
+
 @pytest.mark.parametrize("bad", [7, -1])
 def test_index_out_of_range(bad):
     O = np.arange(3 * 700 + 1, dtype=np.int32)

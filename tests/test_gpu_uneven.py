@@ -112,7 +112,7 @@ def test_prepare_with_few_long_bags():
 # (96K: 2.7 times the even call by tiles merged, 1.3 by table.  The others: 2.0, 1.64
 # and 2.35 where the counts were read in words of two, by tiles of at most 4096; 1.46,
 # 1.29 and 1.26 now.  The limits lie between.)
-@pytest.mark.parametrize("batch,long,each,limit", [(512, 180, 23, 1.9), (4096, 120, 16, 1.72), (8192, 120, 16, 1.46),
+@pytest.mark.parametrize("batch,long,each,limit", [(512, 180, 23, 1.9), (4096, 120, 16, 1.72), (8192, 120, 16, 1.55),
                                                    (16384, 115, 15, 1.75)])
 def test_prepare_of_one_long_table(batch, long, each, limit):
     """Most look-ups in one of 8 tables, against the same number shared by all: a block of the
@@ -121,3 +121,12 @@ def test_prepare_of_one_long_table(batch, long, each, limit):
                  for bags in ([long] + [1] * 7, [each] * 8))
     log(f"[uneven] prepare of {batch * (long + 7)} look-ups over 8 tables: one long {one:.1f} us, even {even:.1f} us")
     assert one <= limit * even
+
+
+# (1.54 times the even call where the walk of a group was 16 look-ups on average, as long
+# as the even one now)
+def test_forward_of_one_long_table():
+    one, even = (Call([100_000] * 26, 2048, bags, 256).us("forward")
+                 for bags in ([100] + [1] * 25, [5] * 26))
+    log(f"[uneven] forward over 26 tables, E=256: one long {one:.1f} us, even {even:.1f} us")
+    assert one <= 1.3 * even
