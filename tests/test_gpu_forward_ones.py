@@ -85,6 +85,27 @@ def test_pooled_bits_of_short_groups(dim, T, batch, avg, kind):
     assert bits_equal(Y.cpu().numpy(), oracle.forward(W, batch, I, O)[1])
 
 
+@pytest.mark.parametrize("dim", [16, 64, 256])
+def test_infinities_and_nan_are_copied(dim):
+    """A row's infinities and NaN reach the bags that name it and no other."""
+    rng = np.random.default_rng(dim)
+    W = [rng.standard_normal((50, dim)).astype(np.float32) for _ in range(3)]
+    W[0][3], W[1][4], W[2][5, 1] = np.inf, np.nan, -np.inf
+    batch = 3000
+    O = np.arange(3 * batch + 1, dtype=np.int32)
+    I = rng.integers(0, 50, 3 * batch).astype(np.int32)
+    a = rng.uniform(-2, 2, I.size).astype(np.float32)
+    gt = GpuTables(W)
+    rc, Y = gt.forward(batch, I, O)
+    ref = np.stack([W[t][I[t * batch:(t + 1) * batch]] for t in range(3)])
+    assert rc == 0 and np.array_equal(Y.cpu().numpy(), ref, equal_nan=True)
+    assert pk.embbag_forward_pooled(gt.w, batch, to_dev(I), to_dev(O), Y, to_dev(a),
+                                    pk.EMBBAG_POOL_SUM, gt.status) == 0
+    ref = (ref.astype(np.float64) * a.reshape(3, batch, 1)).astype(np.float32)
+    assert np.array_equal(Y.cpu().numpy(), ref, equal_nan=True)
+    assert gt.read_status() == 0
+
+
 @pytest.mark.parametrize("bad", [7, -1])
 def test_index_out_of_range(bad):
     O = np.arange(3 * 700 + 1, dtype=np.int32)

@@ -143,8 +143,8 @@ def test_dispatch_block_order():
 @pytest.mark.parametrize("dim,seed", [(16, 1), (64, 2), (64, 3), (256, 4)])
 def test_segments_of_many_lengths(dim, seed):
     """Segments of every length from 1 to tens of thousands of look-ups, in random
-    bags: they start and end at every offset within chunks and within the groups
-    of chunks whose partials are pre-summed, and some fill several whole groups."""
+    bags: they start and end at every offset within chunks and blocks, and some
+    go on over many blocks."""
     rng = np.random.default_rng(1000 + seed)
     M = 400
     mult = np.concatenate([rng.integers(1, 40, 200), rng.integers(40, 3000, 40),
@@ -163,10 +163,9 @@ def test_segments_of_many_lengths(dim, seed):
 
 @pytest.mark.parametrize("dim", [256, 512])
 def test_segment_past_one_flag_read(dim):
-    """One row takes 250K of ~345K look-ups: at E >= 256 (64 lanes per row, chunks
-    of 128 look-ups) its segment fills about 120 groups of 16 chunks, more than
-    the 64 group flags the fix-up reads at a time, so the fix-up reads the next
-    64 flags after a read that found every group filled."""
+    """One row takes 250K of ~345K look-ups: its segment goes on over 1950 blocks of
+    128 look-ups, and its end is found by a search (at E = 512 its blocks are
+    pre-summed in groups of 16)."""
     rng = np.random.default_rng(dim + 5)
     M = 64
     mult = np.concatenate([[250000], rng.integers(1, 3000, M - 1)])
@@ -181,8 +180,8 @@ def test_segment_past_one_flag_read(dim):
     check_step(W, batch, look, O, G, 0.1, what=f"segment past one flag read E={dim}")
 
 
-# chunk length of the sorted look-ups at these sizes (64 lanes per row: 128;
-# 16 lanes: 32; 4 lanes: 8)
+# lengths around which the segments are made: chunks (8 look-ups; 32 at E >= 256)
+# or row groups' blocks
 _CHUNK = {16: 8, 64: 32, 256: 128, 512: 128, 1024: 128}
 
 
@@ -192,13 +191,11 @@ _CHUNK = {16: 8, 64: 32, 256: 128, 512: 128, 1024: 128}
                                             (256, False, "mean"), (256, False, "weighted"),
                                             (512, False, "sum"), (1024, True, "sum")])
 def test_segments_around_the_chunk_length(dim, split, mode):
-    """Segments of 1-3 look-ups, of 63-65 (a 64-lane row's window past a chunk
-    end) and of one, two, three and sixteen chunk lengths and one look-up
-    either side, in random order.  With 64 lanes per row, a segment that ends
-    within the next chunk's first 64 look-ups is summed whole by the chunk
-    where it begins (the next chunk starts after it); all others crossing a
-    boundary go through the partial sums.  Every kind starts at every offset
-    of a chunk."""
+    """Segments of 1-3 look-ups, of 63-65 and of one, two, three and sixteen times
+    a chunk or block and one look-up either side, in random order: a segment is
+    applied by the row group where it begins, with the sums that the following
+    row groups of the block parked, or by the fix-up where it goes on past the
+    block.  Every kind starts at every offset of a chunk."""
     import paper_2005_04680_amd as pk
     c = _CHUNK[dim]
     rng = np.random.default_rng(7 * dim + split + 3 * (mode != "sum"))
