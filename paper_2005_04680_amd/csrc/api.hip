@@ -212,7 +212,9 @@ BwdLayout backward_layout(int32_t T, int32_t B, int64_t NS, int32_t E, uint32_t 
   // table (28) 31.4 / 36.1 / 41.6 / 41.6; 540K weighted of E = 100 (72) 72.1 /
   // 72.8 / 70.9 / 72.0, 1.7M of E = 128 (208) 245 / 247 / 220 / 217, 1.8M of E =
   // 64 88.9 / 90.3 / 92.8 / 97.3, 4.4M of E = 16 100.1 / 97.7 / 95.4 / 94.6, 2M of
-  // E = 16 (32, 16 row groups a wavefront) 64.8 / 57.8 / 55.7 / 55.6.  Beyond 256
+  // E = 16 (32, 16 row groups a wavefront) 64.8 / 57.8 / 55.7 / 55.6.  (At 16 lanes one
+  // round stays the better one past 32 look-ups; the 10% that four give are at 32
+  // lanes.  The line is the same for both.)  Beyond 256
   // long walks lose what fewer block boundaries gain (13.1M of E = 256: 64 1760,
   // 128 1705, 256 1694, 512 1743).
   const RowGeom g = row_geom(E);

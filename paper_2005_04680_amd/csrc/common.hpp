@@ -135,7 +135,12 @@ inline bool dispatch_order(int64_t blocks, int32_t num_tables, int64_t per_table
 }
 
 // The update's order: a table's reused data there is its dY, B rows of E
-// gradients of dy_bytes each.
+// gradients of dy_bytes each.  Its kernels leave room for about half of the blocks
+// that dispatch_order takes for resident (kReduceBlocks); with that number in the
+// rule, calls of 1025 to 2048 blocks with a large dY went to dispatch order and
+// were slower (E = 256, us per update, as here / so: 262K look-ups over 8 tables of
+// 16384 bags 79.2 / 84.0, over 4 of 32768 77.9 / 80.2, over 2 75.9 / 74.5; E = 128, 524K
+// over 8 82.0 / 83.0; more blocks, and the Large shape, the same).
 inline bool apply_in_dispatch_order(int64_t blocks, int32_t T, int32_t B, int32_t E,
                                     int dy_bytes) {
   return dispatch_order(blocks, T, int64_t(B) * E * dy_bytes);
