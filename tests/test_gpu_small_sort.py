@@ -149,6 +149,27 @@ def test_data_errors(counts):
     assert rc == 0 and status == 0
 
 
+def test_data_errors_in_large_tiles():
+    """The same where tiles hold 8192 look-ups."""
+    T, batch, n = 8, 500, 150_000
+    rows = (700,) * T
+    I, O = _batch(np.random.default_rng(4), rows, batch, (n,) * T)
+    bad_row = I.copy()
+    bad_row[5 * n + 8192] = 700
+    offs = [O.copy() for _ in range(4)]
+    offs[0][3 * batch] = -2 ** 31
+    offs[1][3 * batch + 7:3 * batch + 9] = 2 ** 31 - 1
+    offs[2][-1] -= 1
+    offs[3][0] = 1
+    rc, status, _ = gpu_dedup(rows, batch, bad_row, O)
+    assert rc == 0 and status == pk.EMBBAG_ERR_INDEX_RANGE
+    for off in offs:
+        rc, status, _ = gpu_dedup(rows, batch, bad_row, off)
+        assert rc == 0 and status == pk.EMBBAG_ERR_OFFSETS
+    rc, status, _ = gpu_dedup(rows, batch, I, O)
+    assert rc == 0 and status == 0
+
+
 @pytest.mark.parametrize("counts", [(2000, 1500), (9000, 4097), (30000, 4097), (50000, 70000),
                                     (300000, 230000), (490000, 33000)])
 def test_weights_travel_with_the_look_ups(counts):
